@@ -1,0 +1,23 @@
+"""GPU parity at the sizes where a kernel's tiles, masks and dispatch rules
+change: each case is small and compared with the oracle at the same bars as
+the stage and end-to-end parity tests."""
+from dataclasses import replace
+
+import pytest
+
+from gpu_harness import SMALL, inputs
+from test_gpu_parity import _check_end_to_end, _gpu  # noqa: F401  (_gpu: module fixture)
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("fmt4", ["nvfp4", "mxfp4"])
+@pytest.mark.parametrize("n", [1, 4, 15, 16, 17, 31, 32, 33, 48, 49, 63])
+def test_partial_block_masks(n, fmt4, d):
+    """Three one-block frames of n tokens, one 16-bit, one 8-bit and one 4-bit
+    key block per row: every phase masks the padding slots from n on, at both
+    lane halves and both logit tiles."""
+    w = replace(SMALL, name=f"mask-{n}-{fmt4}-d{d}", B=1, H=2, d=d, T=3, Hg=1, Wg=n, partition="ragged", scope="row",
+                num16=34, budgets=(33, 33, 100), fmt4=fmt4)
+    _check_end_to_end(w, *inputs(w))

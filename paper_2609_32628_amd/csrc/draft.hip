@@ -5,6 +5,7 @@
 //                  max|Q|, max|K| used by the NVFP4 tensor scales.
 //   draft_logits   128x128 tiles of Qbar Kbar^T / sqrt d or Qmax Kmax^T / sqrt d
 //                  on the float64 matrix cores (16x16x4 MFMA).
+//   draft_rows     short rows: logits and softmaxes of 16 rows in one workgroup.
 //   draft_softmax  one wave per row: the two row softmaxes (max subtracted)
 //                  mixed with weight lambda, rounded once to float32.
 #include "common.hpp"
@@ -60,18 +61,27 @@ __global__ __launch_bounds__(256) void draft_pool_kernel(DraftArgs args) {
   const int p = tid % CP, q = tid / CP;
   double s0 = 0.0, s1 = 0.0;
   float m0 = -INFINITY, m1 = -INFINITY, am = 0.0f;
+  // A full block needs no test per row: 64 compares and selects of the 340
+  // vector instructions (R = 1,260 x 40 heads, bound by its reads: 333 us
+  // with them in every block, 320 without).
+  auto reduce = [&]<bool FULL>() {
 #pragma unroll
-  for (int r = 0; r < RPQ; ++r) {
-    const int s = q * RPQ + r;
-    const float2 f = tile_pair(tile, D, s, p);
-    if (s < n) {
-      s0 += (double)f.x;
-      s1 += (double)f.y;
+    for (int r = 0; r < RPQ; ++r) {
+      const int s = q * RPQ + r;
+      const float2 f = tile_pair(tile, D, s, p);
+      if (FULL || s < n) {
+        s0 += (double)f.x;
+        s1 += (double)f.y;
+      }
+      m0 = fmaxf(m0, f.x);
+      m1 = fmaxf(m1, f.y);
+      am = fmaxf(am, fmaxf(fabsf(f.x), fabsf(f.y)));
     }
-    m0 = fmaxf(m0, f.x);
-    m1 = fmaxf(m1, f.y);
-    am = fmaxf(am, fmaxf(fabsf(f.x), fabsf(f.y)));
-  }
+  };
+  if (n == kCap)
+    reduce.template operator()<true>();
+  else
+    reduce.template operator()<false>();
   __syncthreads();  // every thread is done with the tile
   s_sum[q][2 * p] = s0;
   s_sum[q][2 * p + 1] = s1;
@@ -115,7 +125,9 @@ typedef double f64x4 __attribute__((ext_vector_type(4)));
 // Each XCD takes whole branches: the descriptors of one (2.6 MB at R = 1,260)
 // fit its L2, while tiles dealt round-robin had every XCD read every branch
 // (L2 hit rate 48%). With the epilogue's multiplication by 1/sqrt(d) instead
-// of a float64 division per logit: 690 -> 660 us at R = 1,260, 40 heads.
+// of a float64 division per logit: 690 -> 660 us at R = 1,260, 40 heads; with
+// quarters inside the matrix stored without bounds checks 627 us (MFMA busy
+// 0.75; all of it busy would be 470).
 constexpr int kLogitTile = 128;  // rows per workgroup
 constexpr int kLogitCols = 160;  // columns per workgroup
 template <int D>
@@ -197,15 +209,22 @@ __global__ __launch_bounds__(256) void draft_logits_kernel(DraftArgs args) {
   }
   // accumulator element e of lane l: row l/16 + 4e, column l%16
   const double rsqd = 1.0 / sqrt((double)d);
+  auto store = [&]<bool INSIDE>() {
 #pragma unroll
-  for (int i = 0; i < NI; ++i)
-#pragma unroll
-    for (int j = 0; j < NJ; ++j)
+    for (int i = 0; i < NI; ++i)
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        const int row = r0 + 16 * i + q + 4 * e, col = c0 + 16 * j + li;
-        if (row < R && col < R) out[(int64_t)row * R + col] = acc[i][j][e] * rsqd;
+        const int row = r0 + 16 * i + q + 4 * e, col = c0 + li;
+        double* o = out + (int64_t)row * R + col;
+#pragma unroll
+        for (int j = 0; j < NJ; ++j)
+          if (INSIDE || (row < R && col + 16 * j < R)) o[16 * j] = acc[i][j][e] * rsqd;
       }
+  };
+  if (r0 + 64 <= R && c0 + 80 <= R)  // the wave's quarter needs no bounds checks
+    store.template operator()<true>();
+  else
+    store.template operator()<false>();
 }
 
 __device__ inline double wave_max_f64(double v) {
@@ -319,6 +338,147 @@ __global__ __launch_bounds__(256) void draft_softmax_kernel(DraftArgs args) {
   for (int i = lane; i < R; i += 64) out[i] = (float)(exp_neg(s1[i] - m1) * r1 + exp_neg(s2[i] - m2) * r2);
 }
 
+// Short rows (R <= 64 KT): one workgroup owns 16 rows of a head, both branches
+// and every column, so the two logit tiles never leave its registers and the
+// row softmaxes follow in the same launch. Wave w holds the column tiles
+// w, w + 4, ... (KT of them); row statistics are reduced over the 16 lanes of
+// an accumulator row, then over the waves through LDS. At these sizes a
+// 128x160 tile per workgroup leaves the chip idle and its one wave round is
+// the time: 12.8 + 4 us for the two launches at R = 8 x 2 heads, 14 + 5 us at
+// R = 70 x 12 heads. Beyond 256 columns a wave would need more than 64
+// accumulator registers, every key operand still feeds one product only, and
+// the tiled kernel wins. Whole draft_map call, two launches against this:
+// R = 8 x 2 heads 19.6 -> 12.8 us, 75 x 12 (d = 128) 35 -> 24, 200 x 12
+// 47 -> 41, 200 x 40 108 -> 103.
+template <int D, int KT>
+__global__ __launch_bounds__(256) void draft_rows_kernel(DraftArgs args) {
+  constexpr int d = D, NT = d / 8;
+  constexpr int PF = KT <= 2 ? 4 : 2;  // channel groups in flight
+  const int R = args.R, bh = blockIdx.y;
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, li = lane & 15, q = lane >> 4;
+  const int r0 = blockIdx.x * 16;
+  __shared__ double s_part[2][4][16];
+  const int64_t base = (int64_t)bh * R * d;
+  const double* Qs[2] = {args.Qbar + base, args.Qmax + base};
+  const double* Ks[2] = {args.Kbar + base, args.Kmax + base};
+  // 32-bit element offsets of each lane's operand rows
+  const int oa = min(r0 + li, R - 1) * d + 2 * q;
+  int ob[KT];
+#pragma unroll
+  for (int k = 0; k < KT; ++k) ob[k] = min(16 * (wave + 4 * k) + li, R - 1) * d + 2 * q;
+  f64x4 acc[2][KT];
+  double2 a[PF][2], b[PF][2][KT];
+#pragma unroll
+  for (int br = 0; br < 2; ++br)
+#pragma unroll
+    for (int k = 0; k < KT; ++k) acc[br][k] = f64x4{0.0, 0.0, 0.0, 0.0};
+  auto load = [&](int t) {
+#pragma unroll
+    for (int br = 0; br < 2; ++br) {
+      a[t % PF][br] = *reinterpret_cast<const double2*>(Qs[br] + oa + 8 * t);
+#pragma unroll
+      for (int k = 0; k < KT; ++k) b[t % PF][br][k] = *reinterpret_cast<const double2*>(Ks[br] + ob[k] + 8 * t);
+    }
+  };
+#pragma unroll
+  for (int t = 0; t < PF; ++t) load(t);
+#pragma unroll
+  for (int t = 0; t < NT; ++t) {
+#pragma unroll
+    for (int br = 0; br < 2; ++br)
+#pragma unroll
+      for (int k = 0; k < KT; ++k)
+        acc[br][k] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[t % PF][br].x, b[t % PF][br][k].x, acc[br][k], 0, 0, 0);
+#pragma unroll
+    for (int br = 0; br < 2; ++br)
+#pragma unroll
+      for (int k = 0; k < KT; ++k)
+        acc[br][k] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[t % PF][br].y, b[t % PF][br][k].y, acc[br][k], 0, 0, 0);
+    if (t + PF < NT) load(t + PF);
+  }
+  // accumulator element e of lane l: row l/16 + 4e, column l%16
+  const double rsqd = 1.0 / sqrt((double)d);
+  // combines v[br][e] over the row's 16 lanes and the four waves
+  auto row_reduce = [&](double (&v)[2][4], auto op) {
+#pragma unroll
+    for (int br = 0; br < 2; ++br)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        for (int o = 8; o > 0; o >>= 1) v[br][e] = op(v[br][e], __shfl_xor(v[br][e], o, 64));
+        if (li == 0) s_part[br][wave][q + 4 * e] = v[br][e];
+      }
+    __syncthreads();
+#pragma unroll
+    for (int br = 0; br < 2; ++br)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int row = q + 4 * e;
+        v[br][e] = op(op(s_part[br][0][row], s_part[br][1][row]), op(s_part[br][2][row], s_part[br][3][row]));
+      }
+    __syncthreads();
+  };
+  double m[2][4], z[2][4];
+#pragma unroll
+  for (int br = 0; br < 2; ++br)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      m[br][e] = -INFINITY;
+#pragma unroll
+      for (int k = 0; k < KT; ++k) {
+        const bool in = 16 * (wave + 4 * k) + li < R;
+        acc[br][k][e] = in ? acc[br][k][e] * rsqd : -INFINITY;
+        m[br][e] = fmax(m[br][e], acc[br][k][e]);
+      }
+    }
+  row_reduce(m, [](double x, double y) { return fmax(x, y); });
+#pragma unroll
+  for (int br = 0; br < 2; ++br)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      z[br][e] = 0.0;
+#pragma unroll
+      for (int k = 0; k < KT; ++k) {
+        const bool in = 16 * (wave + 4 * k) + li < R;
+        acc[br][k][e] = in ? exp_neg(acc[br][k][e] - m[br][e]) : 0.0;
+        z[br][e] += acc[br][k][e];
+      }
+    }
+  row_reduce(z, [](double x, double y) { return x + y; });
+  const double lam = args.lambda;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const int row = r0 + q + 4 * e;
+    const double f1 = (1.0 - lam) / z[0][e], f2 = lam / z[1][e];
+    float* out = args.A + ((int64_t)bh * R + row) * R;
+#pragma unroll
+    for (int k = 0; k < KT; ++k) {
+      const int col = 16 * (wave + 4 * k) + li;
+      if (row < R && col < R) out[col] = (float)(acc[0][k][e] * f1 + acc[1][k][e] * f2);
+    }
+  }
+  // the first workgroup of a head also reduces its per-block max |Q|, max |K|
+  if (blockIdx.x == 0 && wave < 2) {
+    const float* bm = args.blkmax + ((int64_t)wave * args.B * args.H + bh) * R;
+    float t = 0.0f;
+    for (int i = lane; i < R; i += 64) t = fmaxf(t, bm[i]);
+    t = wave_max(t);
+    if (lane == 0) args.stats[(int64_t)bh * (4 + d) + wave] = __float_as_uint(t);
+  }
+}
+
+constexpr int kShortRow = 256;
+
+template <int D>
+void launch_rows(const DraftArgs& args, hipStream_t stream) {
+  const dim3 grid((args.R + 15) / 16, args.B * args.H);
+  if (args.R <= 64)
+    hipLaunchKernelGGL((draft_rows_kernel<D, 1>), grid, dim3(256), 0, stream, args);
+  else if (args.R <= 128)
+    hipLaunchKernelGGL((draft_rows_kernel<D, 2>), grid, dim3(256), 0, stream, args);
+  else
+    hipLaunchKernelGGL((draft_rows_kernel<D, 4>), grid, dim3(256), 0, stream, args);
+}
+
 hipError_t launch_draft(const DraftArgs& args, hipStream_t stream) {
   const int BH = args.B * args.H;
   const dim3 pool_grid(args.R, BH, 2);
@@ -332,6 +492,13 @@ hipError_t launch_draft(const DraftArgs& args, hipStream_t stream) {
       hipLaunchKernelGGL((draft_pool_kernel<64, uint16_t>), pool_grid, dim3(256), 0, stream, args);
     else
       hipLaunchKernelGGL((draft_pool_kernel<64, float>), pool_grid, dim3(256), 0, stream, args);
+  }
+  if (args.R <= kShortRow) {
+    if (args.d == 128)
+      launch_rows<128>(args, stream);
+    else
+      launch_rows<64>(args, stream);
+    return hipGetLastError();
   }
   const int64_t nt = (args.R + kLogitTile - 1) / kLogitTile, ntc = (args.R + kLogitCols - 1) / kLogitCols;
   const dim3 lgrid((unsigned)(8 * ((2 * BH * nt * ntc + 7) / 8)));

@@ -7,6 +7,7 @@ import pytest
 
 from gpu_harness import SMALL, inputs
 from test_gpu_parity import _check_end_to_end, _gpu  # noqa: F401  (_gpu: module fixture)
+from test_gpu_parity import test_draft_map_row_lengths as _check_draft_map
 
 pytestmark = pytest.mark.gpu
 
@@ -21,3 +22,11 @@ def test_partial_block_masks(n, fmt4, d):
     w = replace(SMALL, name=f"mask-{n}-{fmt4}-d{d}", B=1, H=2, d=d, T=3, Hg=1, Wg=n, partition="ragged", scope="row",
                 num16=34, budgets=(33, 33, 100), fmt4=fmt4)
     _check_end_to_end(w, *inputs(w))
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("R", [1, 15, 17, 64, 65, 128, 129, 256, 257])
+def test_draft_map_short_rows(R, d):
+    """R one-block frames: the edges of the short-row kernel's column tiles and
+    the first length that takes the tiled kernel."""
+    _check_draft_map(replace(SMALL, name=f"draft-R{R}-d{d}", B=1, H=2, d=d, T=R, Hg=7, Wg=8))

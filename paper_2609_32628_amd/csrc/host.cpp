@@ -387,9 +387,7 @@ int32_t rank_launch(const float* A, const Dims& d, int32_t num16, int32_t num8, 
   o += align_up(8 * da2::kCuts * d.BH);
   a.cost = reinterpret_cast<int32_t*>(w + o);
   o += align_up(4 * d.BH * d.R);
-  a.cand = reinterpret_cast<uint64_t*>(w + o);
-  o += align_up(8 * d.BH * da2::kCuts * da2::kRankCand);
-  a.ccount = reinterpret_cast<uint32_t*>(w + o);
+  a.obins = reinterpret_cast<uint32_t*>(w + o);
   return hip_status(da2::launch_rank(a, static_cast<hipStream_t>(stream)));
 }
 

@@ -29,7 +29,8 @@ struct DraftArgs {
 
 constexpr int kCuts = 3;  // rank cut points: T16, T16+T8, T16+T8+T4
 
-constexpr int kRankCand = 2048;  // candidate keys per (head, cut) the ranking resolves directly
+// Sizes the bins of the work order live in (48 KB for one head, 32 KB needed).
+constexpr int kRankCand = 2048;
 
 struct RankArgs {
   const float* A;
@@ -42,13 +43,12 @@ struct RankArgs {
   int32_t* order;          // [BH*R]
   int32_t* meta;           // [8]
   // workspace
-  uint32_t* hist;          // [BH][kCuts][2048]
+  uint32_t* hist;          // [BH][kCuts * 2048]: a head's counters
   uint64_t* thr;           // head: [BH][kCuts]; row: [BH*R][kCuts]
-  uint64_t* prefix;        // [BH][kCuts]
-  int64_t* kleft;          // [BH][kCuts]
-  uint64_t* cand;          // [BH][kCuts][kRankCand] keys collected in the third histogram pass
-  uint32_t* ccount;        // [BH][kCuts] number collected (> kRankCand: too many, not used)
-  int32_t* cost;           // [BH*R]
+  uint64_t* prefix;        // [BH][kCuts]: lower ends of the threshold brackets
+  int64_t* kleft;          // [BH][kCuts]: upper ends
+  uint32_t* obins;         // rows per bin of the work order
+  int32_t* cost;           // [BH*R]: row's place inside its bin (long rows: its cost)
 };
 
 struct PrepArgs {

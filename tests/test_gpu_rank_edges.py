@@ -1,0 +1,107 @@
+"""Ranking on the GPU against the oracle's sort over the forms the selection
+takes: row lengths at the edges of its steps and dispatch rules, both scopes,
+and score distributions that are ties, signed, or unlike the sample that the
+head selection brackets its thresholds with."""
+import numpy as np
+import pytest
+import torch
+
+from gpu_harness import lists_of, log
+from oracle import rank as orank
+from paper_2609_32628_amd import api
+
+pytestmark = pytest.mark.gpu
+
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    api.lib()
+
+
+def _sampled(M):
+    """Positions the head selection samples: one hashed place in each of 32,768
+    (8,192 for small heads) equal strata."""
+    SAMPLES = 32768 if M >= 4 * 32768 + 64 else 8192
+    j = np.arange(SAMPLES, dtype=np.uint64)
+    p0, p1 = j * np.uint64(M) // np.uint64(SAMPLES), (j + np.uint64(1)) * np.uint64(M) // np.uint64(SAMPLES)
+    m32 = np.uint64(0xFFFFFFFF)
+    x = ((j + np.uint64(1)) * np.uint64(0x9E3779B1)) & m32
+    x ^= x >> np.uint64(15)
+    x = (x * np.uint64(0x85EBCA77)) & m32
+    x ^= x >> np.uint64(13)
+    return (p0 + (((p1 - p0) * x) >> np.uint64(32))).astype(np.int64)
+
+
+def _scores(kind, R, seed):
+    rng = np.random.default_rng(seed)
+    A = np.exp(3 * rng.standard_normal((R, R))).astype(np.float32)
+    if kind == "softmax":
+        A /= A.sum(axis=1, keepdims=True)
+    elif kind == "constant":
+        A[:] = 0.25
+    elif kind == "ties":      # a spike of equal scores across every usual threshold, zeros of both signs
+        A[rng.random((R, R)) < 0.6] = 1.0
+        A[rng.random((R, R)) < 0.2] = 0.0
+        A[rng.random((R, R)) < 0.1] = -0.0
+    elif kind == "signed":
+        A = rng.standard_normal((R, R)).astype(np.float32)
+        A[0, :min(R, 3)] = [np.inf, -np.inf, 1e-42][:min(R, 3)]
+    elif kind == "unsampled-high":   # every sampled score is below every other one: all brackets miss
+        A.reshape(-1)[_sampled(R * R)] = 1e-20
+    elif kind == "unsampled-inside":  # all other scores lie inside the brackets: the gathered keys do not fit
+        A[:] = rng.random((R, R)).astype(np.float32) * 1e-3 + 0.5
+        A.reshape(-1)[_sampled(R * R)] = np.linspace(0.0, 1.0, _sampled(R * R).size, dtype=np.float32)
+    return A
+
+
+def _check(R, scope, kind, budgets, H=2):
+    num16, num8, num4, den = budgets
+    log(f"ranking R={R} {scope} {kind} {budgets}")
+    p = api.problem(1, H, 64, R, 7, 8)
+    buf = api.alloc(p, scope)
+    A = np.stack([_scores(kind, R, 10 * R + h) for h in range(H)])
+    buf.A.copy_(torch.from_numpy(A[None]))
+    buf.cls.fill_(0xA5)
+    buf.lists.fill_(0xA5)
+    api.da2_rank_assign(buf.A, p, num16, num8, num4, den, scope, buf.cls, buf.lists, buf.ws_rank)
+    torch.cuda.synchronize()
+    cls = buf.cls.cpu().numpy().reshape(H, R, R)
+    keys, counts, order = lists_of(buf, p)
+    assert np.array_equal(np.sort(order), np.arange(H * R))
+    for h in range(H):
+        want = orank.rank_head(A[h], num8, num4, den, scope, num16=num16)
+        assert np.array_equal(cls[h], want), h
+        for a in range(R):
+            row = h * R + a
+            lists = orank.key_lists_all(want[a])
+            assert [len(x) for x in lists] == list(counts[row, :3]) and counts[row, 3] == 0
+            assert np.array_equal(keys[row, :counts[row, :3].sum()], np.concatenate(lists))
+
+
+BUDGETS = (15, 10, 30, 100)
+
+
+@pytest.mark.parametrize("scope", ["head", "row"])
+@pytest.mark.parametrize("R", [1, 2, 3, 63, 64, 65, 181, 182, 255, 256, 257, 362, 363, 513, 768, 769])
+def test_row_lengths(R, scope):
+    """Edges of the 256-pair steps, of the direct selection (R = 181) and of
+    the larger sample (R = 363); rows start at odd addresses."""
+    _check(R, scope, "softmax", BUDGETS)
+
+
+@pytest.mark.parametrize("kind", ["constant", "ties", "signed", "unsampled-high", "unsampled-inside"])
+@pytest.mark.parametrize("R,scope", [(150, "head"), (200, "head"), (530, "head"), (1500, "head"), (530, "row")])
+def test_distributions(R, scope, kind):
+    if R == 150 and kind.startswith("unsampled"):
+        pytest.skip("this head is selected without a sample")
+    for budgets in (BUDGETS, (0, 10, 30, 100), (0, 0, 50, 100), (1, 998, 0, 1000), (100, 0, 0, 100), (0, 0, 0, 100)):
+        _check(R, scope, kind, budgets, H=1)
+
+
+@pytest.mark.parametrize("R,scope", [(2047, "head"), (2048, "row"), (2049, "row")])
+def test_longest_rows(R, scope):
+    """The longest head (2^22 pairs less) and row of the register kernels, and
+    the first row that is sorted in LDS."""
+    _check(R, scope, "softmax", BUDGETS, H=1)

@@ -1,7 +1,7 @@
 // Operand preparation kernels (format appendix; NVFP4 quantization equation).
 //
-//   prep_vstats  token-major pass over V of each head: per-channel max|V| and
-//                the head's max|V| (every token is a valid key).
+//   prep_vstats  token-major pass over V of each head: per-channel max|V| (every
+//                token is a valid key; small heads: inside prep_qk's launch).
 //   prep_qk      one workgroup per (block, head, Q or K): gathers the block's
 //                64 slots through slot2tok in 16-byte loads (unconditional, so
 //                they overlap; padding slots are masked to 0);
@@ -33,13 +33,63 @@
 
 namespace da2 {
 
-__global__ void zero_vstats_kernel(uint32_t* stats, int d) {
-  uint32_t* s = stats + (int64_t)blockIdx.x * (4 + d);
-  for (int i = 2 + threadIdx.x; i < 4 + d; i += blockDim.x) s[i] = 0u;
-}
-
 // ---- V statistics -----------------------------------------------------------
+// Per-channel max|V| of every head. Large heads: a launch clears the entries and
+// prep_vstats takes chunks of tokens with one atomic max per channel (before
+// prep_qk: after it, the pass waits for prep_qk's writes, 26 instead of 16 us on
+// 32,760 tokens x 12 heads, more than the clearing launch costs). Small heads (V
+// of at most kVstatSmall bytes): kVstatParts extra workgroups of the prep_qk
+// launch take a part of the channels each, over all tokens, and store their
+// maxima, which saves both launches (whole layer: 512 tokens x 2 heads 48 -> 42
+// us, 4,255 x 12, d = 64, 105 -> 103; at that size the parts take as long as
+// prep_qk itself). prep_v derives the head's max|V| from the channels'.
+__global__ void zero_vstats_kernel(uint32_t* stats, int d) {
+  stats[(int64_t)blockIdx.x * (4 + d) + 4 + threadIdx.x] = 0u;
+}
 constexpr int kVstatRows = 1024;  // tokens per workgroup (one atomic max per channel per workgroup)
+constexpr int kVstatParts = 4;
+constexpr int64_t kVstatSmall = 1 << 20;
+
+template <int D, typename T>
+__device__ inline void vstats_part(const PrepArgs& args, int bh, int part) {
+  constexpr int EPC = 16 / sizeof(T);          // elements per 16-byte load
+  constexpr int CPP = D / EPC / kVstatParts;   // loads per token row of a part
+  constexpr int RG = 256 / CPP;                // rows per round
+  constexpr int RPR = 16;                      // rows per thread in flight
+  __shared__ float s_max[4][D / kVstatParts];
+  const int b = bh / args.H, h = bh % args.H, tid = threadIdx.x;
+  const int cc = tid % CPP, rg = tid / CPP;
+  const T* X = static_cast<const T*>(args.V) + (int64_t)b * args.sb + (int64_t)h * args.sh +
+               (part * CPP + cc) * EPC;
+  float m[EPC];
+#pragma unroll
+  for (int e = 0; e < EPC; ++e) m[e] = 0.0f;
+#pragma unroll 1
+  for (int t0 = rg; t0 < args.N; t0 += RG * RPR) {
+    uint4 raw[RPR];  // rows past the end read the last token again
+#pragma unroll
+    for (int k = 0; k < RPR; ++k)
+      raw[k] = *reinterpret_cast<const uint4*>(X + (int64_t)min(t0 + RG * k, args.N - 1) * args.sn);
+#pragma unroll
+    for (int k = 0; k < RPR; ++k) {
+      float x[EPC];
+      chunk_floats<T>(raw[k], x);
+#pragma unroll
+      for (int e = 0; e < EPC; ++e) m[e] = fmaxf(m[e], fabsf(x[e]));
+    }
+  }
+#pragma unroll
+  for (int o = CPP; o < 64; o <<= 1)
+#pragma unroll
+    for (int e = 0; e < EPC; ++e) m[e] = fmaxf(m[e], __shfl_xor(m[e], o, 64));
+  if ((tid & 63) < CPP)
+#pragma unroll
+    for (int e = 0; e < EPC; ++e) s_max[tid >> 6][cc * EPC + e] = m[e];
+  __syncthreads();
+  if (tid < D / kVstatParts)
+    args.stats[(int64_t)bh * (4 + D) + 4 + part * (D / kVstatParts) + tid] =
+        __float_as_uint(fmaxf(fmaxf(s_max[0][tid], s_max[1][tid]), fmaxf(s_max[2][tid], s_max[3][tid])));
+}
 
 template <int D, typename T>
 __global__ __launch_bounds__(256) void prep_vstats_kernel(PrepArgs args) {
@@ -50,7 +100,6 @@ __global__ __launch_bounds__(256) void prep_vstats_kernel(PrepArgs args) {
   constexpr int ROUNDS = kVstatRows / (RG * RPR);
   static_assert(ROUNDS * RG * RPR == kVstatRows, "whole rounds");
   __shared__ float s_max[4][D];
-  __shared__ float s_all[4];
   const int bh = blockIdx.y, b = bh / args.H, h = bh % args.H, tid = threadIdx.x;
   const int cc = tid % CPR, rg = tid / CPR;
   const int t0 = blockIdx.x * kVstatRows;
@@ -88,16 +137,7 @@ __global__ __launch_bounds__(256) void prep_vstats_kernel(PrepArgs args) {
   __syncthreads();
   if (tid < D) {
     const float t = fmaxf(fmaxf(s_max[0][tid], s_max[1][tid]), fmaxf(s_max[2][tid], s_max[3][tid]));
-    uint32_t* st = args.stats + (int64_t)bh * (4 + D);
-    atomic_max_pos(st + 4 + tid, t);
-    const float wm = wave_max(t);
-    if ((tid & 63) == 0) s_all[tid >> 6] = wm;
-  }
-  __syncthreads();
-  if (tid == 0) {
-    float t = s_all[0];
-    for (int q = 1; q < D / 64; ++q) t = fmaxf(t, s_all[q]);
-    atomic_max_pos(args.stats + (int64_t)bh * (4 + D) + 2, t);
+    atomic_max_pos(args.stats + (int64_t)bh * (4 + D) + 4 + tid, t);
   }
 }
 
@@ -186,6 +226,10 @@ __global__ __launch_bounds__(256) void prep_qk_kernel(PrepArgs args) {
   __shared__ float s_red[4];
   const int a = blockIdx.x, bh = blockIdx.y, which = blockIdx.z;  // which: 0 = Q, 1 = K
   const int b = bh / args.H, h = bh % args.H, R = args.R, tid = threadIdx.x;
+  if (a >= R) {  // extra workgroups of small heads
+    if (which == 0) vstats_part<D, T>(args, bh, a - R);
+    return;
+  }
   const Layout L = layout_view(args.layout, R, args.Npad);
   const int n = L.n_a[a];
   const int32_t* slots = L.slot2tok + (int64_t)a * kCap;
@@ -315,10 +359,14 @@ __global__ __launch_bounds__(256) void prep_v_kernel(PrepArgs args) {
     const uint4 x = *reinterpret_cast<const uint4*>(X + (int64_t)tok[k] * args.sn + cc * EPC);
     v[k] = masked(x, lane_mask(s < n));
   }
-  // this thread's statistics (the head's NVFP4 amax and the amax of channels
-  // p and p + D/2), loaded beside the tile rather than after the barrier
+  // this thread's statistics (the amax of channels p and p + D/2) and the
+  // head's amax over all of them, loaded beside the tile rather than after the
+  // barrier (the values are not negative: their bits order like they do)
   const int p = tid % (D / 2), sg = tid / (D / 2);
-  const uint32_t st_g = st[2], st_c0 = st[4 + p], st_c1 = st[4 + p + D / 2];
+  const uint32_t st_c0 = st[4 + p], st_c1 = st[4 + p + D / 2];
+  uint32_t st_g = st[4 + (tid & 63)];
+  if (D == 128) st_g = max(st_g, st[68 + (tid & 63)]);
+  for (int o = 32; o > 0; o >>= 1) st_g = max(st_g, (uint32_t)__shfl_xor(st_g, o, 64));
 #pragma unroll
   for (int k = 0; k < LPT; ++k) {
     const int ci = tid + 256 * k;
@@ -412,17 +460,23 @@ __global__ __launch_bounds__(256) void prep_v_kernel(PrepArgs args) {
   }
   if (a == 0) {
     if (tid < D) args.dV[(int64_t)bh * D + tid] = __fdiv_rn(__uint_as_float(st[4 + tid]), 2.25f);
-    if (tid < 4) args.g[(int64_t)bh * 4 + tid] = tid < 3 ? nvfp4_scale_global(st[tid]) : __uint_as_float(args.tag);
+    if (tid < 4)
+      args.g[(int64_t)bh * 4 + tid] =
+          tid < 3 ? nvfp4_scale_global(tid == 2 ? st_g : st[tid]) : __uint_as_float(args.tag);
+    if (tid == 2 || tid == 3) args.stats[(int64_t)bh * (4 + D) + tid] = tid == 2 ? st_g : 0u;
   }
 }
 
 template <int D, typename T>
 void launch_prep_t(const PrepArgs& args, hipStream_t stream) {
   const int BH = args.B * args.H;
-  hipLaunchKernelGGL(zero_vstats_kernel, dim3(BH), dim3(64), 0, stream, args.stats, args.d);
-  hipLaunchKernelGGL((prep_vstats_kernel<D, T>), dim3((args.N + kVstatRows - 1) / kVstatRows, BH), dim3(256), 0,
-                     stream, args);
-  hipLaunchKernelGGL((prep_qk_kernel<D, T>), dim3(args.R, BH, 2), dim3(256), 0, stream, args);
+  const bool small = (int64_t)args.N * D * (int64_t)sizeof(T) <= kVstatSmall;
+  if (!small) {
+    hipLaunchKernelGGL(zero_vstats_kernel, dim3(BH), dim3(D), 0, stream, args.stats, args.d);
+    hipLaunchKernelGGL((prep_vstats_kernel<D, T>), dim3((args.N + kVstatRows - 1) / kVstatRows, BH), dim3(256), 0,
+                       stream, args);
+  }
+  hipLaunchKernelGGL((prep_qk_kernel<D, T>), dim3(args.R + (small ? kVstatParts : 0), BH, 2), dim3(256), 0, stream, args);
   hipLaunchKernelGGL((prep_v_kernel<D, T>), dim3(args.R, BH), dim3(256), 0, stream, args);
 }
 

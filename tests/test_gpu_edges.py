@@ -7,7 +7,7 @@ import pytest
 
 from gpu_harness import SMALL, inputs
 from test_gpu_parity import _check_end_to_end, _gpu  # noqa: F401  (_gpu: module fixture)
-from test_gpu_parity import test_draft_map_row_lengths as _check_draft_map
+from test_gpu_parity import test_draft_map_row_lengths as _check_draft_map, test_prep_operands as _check_operands
 
 pytestmark = pytest.mark.gpu
 
@@ -30,3 +30,13 @@ def test_draft_map_short_rows(R, d):
     """R one-block frames: the edges of the short-row kernel's column tiles and
     the first length that takes the tiled kernel."""
     _check_draft_map(replace(SMALL, name=f"draft-R{R}-d{d}", B=1, H=2, d=d, T=R, Hg=7, Wg=8))
+
+
+@pytest.mark.parametrize("dtype,d,n", [("fp32", 128, 2048), ("fp32", 128, 2049), ("fp32", 64, 4096), ("fp32", 64, 4097),
+                                       ("bf16", 128, 4096), ("bf16", 128, 4097), ("bf16", 64, 1), ("bf16", 64, 1025)])
+def test_value_statistics_split(dtype, d, n):
+    """Heads whose V has up to 1 MiB take their channel maxima inside the Q/K
+    launch, larger ones in launches of their own: both sides of the limit, one
+    token, and one token beyond a whole round of loads."""
+    _check_operands(replace(SMALL, name=f"vstats-{dtype}-d{d}-n{n}", B=1, H=2, d=d, T=1, Hg=1, Wg=n, dtype=dtype,
+                            partition="ragged"))

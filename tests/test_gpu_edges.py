@@ -40,3 +40,11 @@ def test_value_statistics_split(dtype, d, n):
     token, and one token beyond a whole round of loads."""
     _check_operands(replace(SMALL, name=f"vstats-{dtype}-d{d}-n{n}", B=1, H=2, d=d, T=1, Hg=1, Wg=n, dtype=dtype,
                             partition="ragged"))
+
+
+@pytest.mark.parametrize("B,H,T", [(1, 1, 1), (1, 1, 9), (1, 2, 5), (1, 3, 7), (1, 5, 11), (1, 7, 4), (3, 3, 13)])
+def test_rows_dealt_to_xcds(B, H, T):
+    """Head counts whose half-heads the eight segments of the work order cut in
+    none, two or more parts: every row is computed."""
+    w = replace(SMALL, name=f"deal-{B}x{H}x{T}", B=B, H=H, T=T, Hg=8, Wg=8, scope="head")
+    _check_end_to_end(w, *inputs(w))

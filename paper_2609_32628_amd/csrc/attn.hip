@@ -56,7 +56,7 @@ typedef __attribute__((address_space(3))) void* lds_ptr;
 // instruction adds its immediate offset to the LDS address in M0 as well).
 // Issued as inline assembly so that the compiler does not add its conservative
 // "wait for every LDS copy" before later LDS reads; the kernel waits for
-// exactly the copies it needs (wait_vmem_keep) instead.
+// its copies itself (wait_vmem) instead.
 template <int OFS>
 __device__ inline void dma_fragment(const void* tile, uint32_t voff, uint32_t lds) {
   static_assert(OFS >= 0 && OFS < 4096, "immediate offset out of range");
@@ -199,18 +199,17 @@ __device__ inline float fp8_weights8(const f32x16& S, float cb, float off, int& 
   return sum;
 }
 
-// 16-bit path weights of 8 logits S[I0..I0+8) of this lane: Pt = 2^(S c - mn)
-// in fp32 (added to sum) and rounded to nearest-even fp16 for the P^T operand.
-template <int I0>
-__device__ inline f16x8 half_weights8(const f32x16& S, float c, float mn, float& sum) {
-  f16x8 h;
+// 16-bit path weights of the logits S[I0..I1) of this lane (within one group of
+// eight): Pt = 2^(S c - mn) in fp32 (added to sum) and rounded to nearest-even
+// fp16 into the group's P^T operand.
+template <int I0, int I1>
+__device__ inline void half_weights(const f32x16& S, float c, float mn, float& sum, f16x8& h) {
 #pragma unroll
-  for (int e = 0; e < 8; ++e) {
-    const float y = exp2_fast(__builtin_fmaf(S[I0 + e], c, -mn));
+  for (int e = I0; e < I1; ++e) {
+    const float y = exp2_fast(__builtin_fmaf(S[e], c, -mn));
     sum += y;
-    h[e] = (_Float16)y;
+    h[e & 7] = (_Float16)y;
   }
-  return h;
 }
 
 // MXFP4 path: D += A B on one 32x32x64 scaled fp4 MFMA. a, b: 32 E2M1 codes
@@ -305,33 +304,6 @@ __device__ inline KeyWin key_window(const uint16_t* list, int first, int count, 
 __device__ inline int lane_value(int v, int lane) { return __builtin_amdgcn_readlane(v, lane); }
 __device__ inline float lane_value(float v, int lane) {
   return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), lane));
-}
-
-// Waits for this wave's older vector-memory operations, leaving the N most
-// recent ones in flight (they complete in issue order).
-template <int N>
-__device__ inline void wait_vmem_keep() {
-  if constexpr (N == 0) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-  else if constexpr (N == 1) asm volatile("s_waitcnt vmcnt(1)" ::: "memory");
-  else if constexpr (N == 2) asm volatile("s_waitcnt vmcnt(2)" ::: "memory");
-  else if constexpr (N == 3) asm volatile("s_waitcnt vmcnt(3)" ::: "memory");
-  else if constexpr (N == 4) asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
-  else if constexpr (N == 8) asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
-  else static_assert(N == 0, "unsupported count");
-}
-// Waits until only the fragments of the most recent tile copy that this wave
-// issued are in flight: NFK/2 each for even NFK; for odd NFK wave 0 copies
-// (NFK+1)/2 fragments and wave 1 the rest.
-template <int NFK>
-__device__ inline void wait_keep_tile(int wave) {
-  if constexpr (NFK % 2 == 0) {
-    wait_vmem_keep<NFK / 2>();
-  } else {
-    if (wave == 0)
-      wait_vmem_keep<(NFK + 1) / 2>();
-    else
-      wait_vmem_keep<NFK / 2>();
-  }
 }
 
 // Workgroup barrier without the memory fences of __syncthreads (the waits
@@ -494,24 +466,29 @@ __device__ inline void nv_phase_loop(const uint16_t* list, int n, const int32_t*
   }
 }
 
-// One precision phase of the block loop, software-pipelined by one block: the
-// logits of block i+1 are computed while the softmax of block i runs, so the
-// matrix cores and the vector ALUs work side by side inside each wave. The
-// workgroup's two waves own the query tiles qt = 0, 1 of the query block; the
-// key and value tiles of each key block are copied into LDS once (each wave
-// issues half of the fragments) and read by both waves. Iteration i:
-//   wait K(i+1) -> barrier -> S' = K(i+1) Q^T interleaved with the first part
-//   of the softmax of S -> barrier -> DMA K(i+2) -> rest of the softmax
-//   -> wait V(i) -> barrier -> U += V(i)^T P^T -> barrier -> DMA V(i+1)
+// The 16-bit phase's block loop, software-pipelined by one block: the logits of
+// block i+1 are computed while the softmax of block i runs, so the matrix cores
+// and the vector ALUs work side by side inside each wave. The workgroup's two
+// waves own the query tiles qt = 0, 1 of the query block; the key and value
+// tiles of each key block are copied into LDS once (each wave issues half of
+// the fragments) and read by both waves. One K and one V tile fit (16 KB each
+// at d = 128). Iteration i:
+//   wait K(i+1) -> barrier -> copy V(i) -> region 1: S' = K(i+1) Q^T beside the
+//   first half of the softmax of S
+//   -> wait V(i) -> barrier -> copy K(i+2) -> U += V(i)^T P^T beside the second
+//   half
+// Two barriers per block, and each copy has one region to arrive. With the
+// second half of the softmax in a stage of its own and four barriers, no matrix
+// work ran beside it: 588 blocks x 12 heads, 40% of the pairs 16-bit, 4.07 ->
+// 3.83 ms at d = 128 and 2.28 -> 2.13 at d = 64; all pairs 9.33 -> 8.78. Bit-
+// identical outputs.
 // Frag: fragment type; NFK: fragments per K (and V) tile; SA: logit tile type.
-// first(S): logits of the first block. region1<MASK>(S, S', nb, dk): the
-// logit MFMAs of block i+1 interleaved with the first part of the softmax of
-// block i (MASK: block i is partial); region2(S): the rest of the softmax, after
-// sK has been handed to the next copy. pv(S): the value product of block i.
-template <int NFK, typename Frag, typename SA, typename FIRST, typename STEP1, typename STEP2, typename PV>
+// first(S): logits of the first block. region1<MASK>(S, S', nb) (MASK: block i
+// is partial); pv(S): the value product of block i.
+template <int NFK, typename Frag, typename SA, typename FIRST, typename STEP1, typename PV>
 __device__ inline void phase_loop(const uint16_t* list, int n, const int32_t* n_a, const float* dKh,
                                   const Frag* Kh, const Frag* Vh, Frag* sK, Frag* sV, int wave, int lane,
-                                  FIRST first_qk, STEP1 region1, STEP2 region2, PV pv) {
+                                  FIRST first_qk, STEP1 region1, PV pv) {
   constexpr int TILE = NFK * 64;       // fragments per tile
   constexpr int W0 = (NFK + 1) / 2;    // fragments wave 0 copies; wave 1 copies the rest
   // Wave 0 copies fragments [0, W0) of a tile, wave 1 the rest; fragment i of
@@ -531,49 +508,39 @@ __device__ inline void phase_loop(const uint16_t* list, int n, const int32_t* n_
   auto block_at = [&](int e, int first) -> int {  // e - first < 128
     return e - first < 64 ? lane_value(win.kb, e - first) : lane_value(win.kb_next, e - first - 64);
   };
-  // prologue: logits of block 0, then K(1) and V(0) in flight
-  const int kb0 = lane_value(win.kb, 0);
-  dma_tile(Kh + (int64_t)kb0 * TILE, sK);
-  wait_vmem_keep<0>();
+  // prologue: logits of block 0, then K(1) in flight
+  dma_tile(Kh + (int64_t)lane_value(win.kb, 0) * TILE, sK);
+  wait_vmem();
   wg_barrier();
   SA Sa, Sb;
   first_qk(Sa);
   wait_lds();
   wg_barrier();
   if (n > 1) dma_tile(Kh + (int64_t)block_at(1, 0) * TILE, sK);
-  dma_tile(Vh + (int64_t)kb0 * TILE, sV);
 
   auto step = [&](int it, SA& Sc, SA& Sn) {
     const int first = it & ~63;
     const int sl = it - first;
     if (sl == 0 && it > 0) win = key_window(list, it, n, n_a, dKh, lane);
     const int nb = lane_value(win.nb, sl);
-    const float dk = lane_value(win.dk, sl);
-    const bool more1 = it + 1 < n, more2 = it + 2 < n;
-    const int kb1 = more1 ? block_at(it + 1, first) : 0;
+    const int kb0 = lane_value(win.kb, sl);
+    const bool more2 = it + 2 < n;
     const int kb2 = more2 ? block_at(it + 2, first) : 0;
-    // K(i+1) copied (V(i), issued later, may still be in flight). On the last
-    // block the logits of the region are computed from the unchanged tile and
-    // not used.
-    wait_keep_tile<NFK>(wave);
-    wg_barrier();
+    wait_vmem();
+    wait_lds();
+    wg_barrier();  // K(i+1) copied; both waves are done with sV
+    dma_tile(Vh + (int64_t)kb0 * TILE, sV);
+    // On the last block the logits of the region are computed from the
+    // unchanged tile and not used.
     if (nb < kCap)
-      region1.template operator()<true>(Sc, Sn, nb, dk);
+      region1.template operator()<true>(Sc, Sn, nb);
     else
-      region1.template operator()<false>(Sc, Sn, nb, dk);
+      region1.template operator()<false>(Sc, Sn, nb);
+    wait_vmem();
     wait_lds();
-    wg_barrier();  // both waves are done with sK
+    wg_barrier();  // V(i) copied; both waves are done with sK
     if (more2) dma_tile(Kh + (int64_t)kb2 * TILE, sK);
-    region2(Sc);  // returns after its results exist, so the wait below stays after it
-    if (more2)
-      wait_keep_tile<NFK>(wave);  // V(i) copied, K(i+2) may still be in flight
-    else
-      wait_vmem_keep<0>();
-    wg_barrier();
     pv(Sc);
-    wait_lds();
-    wg_barrier();  // both waves are done with sV
-    if (more1) dma_tile(Vh + (int64_t)kb1 * TILE, sV);
   };
   for (int it = 0; it < n; it += 2) {
     step(it, Sa, Sb);
@@ -1122,7 +1089,7 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(2))) void m
     float gm0 = 0.0f, gm1 = 0.0f, mn = 0.0f, sum0 = 0.0f, sum1 = 0.0f;
     // Region 1: logits of the next block with the maxima and the first
     // group's weights of the current block (four pieces over the stages).
-    auto region1 = [&]<bool MASK>(SA& Sc, SA& Sn, int nb, float) {
+    auto region1 = [&]<bool MASK>(SA& Sc, SA& Sn, int nb) {
       if constexpr (MASK) mask_tail(Sc, nb, row_slot(r), row_slot(r) + 32, lane);
       f16x8 k0 = sK[lane], k1 = sK[NS16 * 64 + lane];
       constexpr int NP = 4;
@@ -1145,9 +1112,9 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(2))) void m
             gm1 = max16(Sc[1]);
             mn = new_max(fmaxf(gm0, gm1), c16, m, l, alpha);
           } else if (piece == 2) {
-            P[0] = half_weights8<0>(Sc[0], c16, mn, sum0);
+            half_weights<0, 8>(Sc[0], c16, mn, sum0, P[0]);
           } else {
-            P[1] = half_weights8<8>(Sc[0], c16, mn, sum0);
+            half_weights<8, 16>(Sc[0], c16, mn, sum0, P[1]);
           }
         }
         fence();
@@ -1155,20 +1122,14 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(2))) void m
         k1 = n1;
       }
     };
-    // Region 2: the second group's weights.
-    auto region2 = [&](SA& Sc) {
-      sum1 = 0.0f;
-      P[2] = half_weights8<0>(Sc[1], c16, mn, sum1);
-      P[3] = half_weights8<8>(Sc[1], c16, mn, sum1);
-      l += sum0 + sum1;
-      after(P[0]), after(P[1]), after(P[2]), after(P[3]), after(l);
-    };
-    // U += V^T P^T; value fragments are read two MFMAs ahead.
+    // U += V^T P^T; value fragments are read two MFMAs ahead. The MFMAs of the
+    // first group (k < 2 NT) carry the second group's weights.
     auto pv = [&](SA& Sc) {
       if (__ballot(alpha != 1.0f)) rescale<NT>(U, alpha);
       constexpr int NM = 4 * NT;
       auto vfrag = [&](int k) { return sV[((k % NT) * 4 + k / NT) * 64 + lane]; };
       f16x8 v0 = vfrag(0), v1 = vfrag(1);
+      sum1 = 0.0f;
 #pragma unroll
       for (int k = 0; k < NM; ++k) {
         const f16x8 cur = (k & 1) ? v1 : v0;
@@ -1179,6 +1140,16 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(2))) void m
             v0 = vfrag(k + 2);
         }
         U[k % NT] = __builtin_amdgcn_mfma_f32_32x32x16_f16(cur, P[k / NT], U[k % NT], 0, 0, 0);
+        // each piece's results are used in its stage, which keeps the piece there
+        constexpr int NG = 2 * NT;  // MFMAs that read P[0], P[1]
+        if (k == 0) half_weights<0, 4>(Sc[1], c16, mn, sum1, P[2]), after(sum1);
+        if (k == NG / 4) half_weights<4, 8>(Sc[1], c16, mn, sum1, P[2]), after(sum1), after(P[2]);
+        if (k == NG / 2) half_weights<8, 12>(Sc[1], c16, mn, sum1, P[3]), after(sum1);
+        if (k == 3 * NG / 4) {
+          half_weights<12, 16>(Sc[1], c16, mn, sum1, P[3]);
+          l += sum0 + sum1;
+          after(l), after(P[3]);
+        }
         fence();
       }
     };
@@ -1187,7 +1158,7 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(2))) void m
     phase_loop<2 * NS16, f16x8, SA>(keys + n4 + n8, n16, L.n_a, dKh,
                                     reinterpret_cast<const f16x8*>(args.K16) + blk0 * (kCap * D / 8),
                                     reinterpret_cast<const f16x8*>(args.V16) + blk0 * (kCap * D / 8), sK, sV, wave,
-                                    lane, qk, region1, region2, pv);
+                                    lane, qk, region1, pv);
   }
 
   // ------------------------- normalize and scatter -------------------------

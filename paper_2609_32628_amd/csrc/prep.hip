@@ -42,9 +42,12 @@ namespace da2 {
 // launch take a part of the channels each, over all tokens, and store their
 // maxima, which saves both launches (whole layer: 512 tokens x 2 heads 48 -> 42
 // us, 4,255 x 12, d = 64, 105 -> 103; at that size the parts take as long as
-// prep_qk itself). prep_v derives the head's max|V| from the channels'.
+// prep_qk itself), and prep_v derives the head's max|V| from the channels' (in
+// large heads that costs each of prep_v's workgroups more than the atomic: 130.6
+// against 132.7 us for the call on the 12 heads).
 __global__ void zero_vstats_kernel(uint32_t* stats, int d) {
-  stats[(int64_t)blockIdx.x * (4 + d) + 4 + threadIdx.x] = 0u;
+  uint32_t* s = stats + (int64_t)blockIdx.x * (4 + d);
+  for (int i = 2 + threadIdx.x; i < 4 + d; i += blockDim.x) s[i] = 0u;
 }
 constexpr int kVstatRows = 1024;  // tokens per workgroup (one atomic max per channel per workgroup)
 constexpr int kVstatParts = 4;
@@ -100,6 +103,7 @@ __global__ __launch_bounds__(256) void prep_vstats_kernel(PrepArgs args) {
   constexpr int ROUNDS = kVstatRows / (RG * RPR);
   static_assert(ROUNDS * RG * RPR == kVstatRows, "whole rounds");
   __shared__ float s_max[4][D];
+  __shared__ float s_all[4];
   const int bh = blockIdx.y, b = bh / args.H, h = bh % args.H, tid = threadIdx.x;
   const int cc = tid % CPR, rg = tid / CPR;
   const int t0 = blockIdx.x * kVstatRows;
@@ -138,6 +142,14 @@ __global__ __launch_bounds__(256) void prep_vstats_kernel(PrepArgs args) {
   if (tid < D) {
     const float t = fmaxf(fmaxf(s_max[0][tid], s_max[1][tid]), fmaxf(s_max[2][tid], s_max[3][tid]));
     atomic_max_pos(args.stats + (int64_t)bh * (4 + D) + 4 + tid, t);
+    const float wm = wave_max(t);
+    if ((tid & 63) == 0) s_all[tid >> 6] = wm;
+  }
+  __syncthreads();
+  if (tid == 0) {
+    float t = s_all[0];
+    for (int q = 1; q < D / 64; ++q) t = fmaxf(t, s_all[q]);
+    atomic_max_pos(args.stats + (int64_t)bh * (4 + D) + 2, t);
   }
 }
 
@@ -359,14 +371,17 @@ __global__ __launch_bounds__(256) void prep_v_kernel(PrepArgs args) {
     const uint4 x = *reinterpret_cast<const uint4*>(X + (int64_t)tok[k] * args.sn + cc * EPC);
     v[k] = masked(x, lane_mask(s < n));
   }
-  // this thread's statistics (the amax of channels p and p + D/2) and the
-  // head's amax over all of them, loaded beside the tile rather than after the
-  // barrier (the values are not negative: their bits order like they do)
+  // this thread's statistics (the head's NVFP4 amax and the amax of channels
+  // p and p + D/2), loaded beside the tile rather than after the barrier; a
+  // small head's amax comes from its channels' (the values are not negative, so
+  // their bits order like they do)
   const int p = tid % (D / 2), sg = tid / (D / 2);
   const uint32_t st_c0 = st[4 + p], st_c1 = st[4 + p + D / 2];
-  uint32_t st_g = st[4 + (tid & 63)];
-  if (D == 128) st_g = max(st_g, st[68 + (tid & 63)]);
-  for (int o = 32; o > 0; o >>= 1) st_g = max(st_g, (uint32_t)__shfl_xor(st_g, o, 64));
+  uint32_t st_g = st[args.vparts ? 4 + (tid & 63) : 2];
+  if (args.vparts) {
+    if (D == 128) st_g = max(st_g, st[68 + (tid & 63)]);
+    for (int o = 32; o > 0; o >>= 1) st_g = max(st_g, (uint32_t)__shfl_xor(st_g, o, 64));
+  }
 #pragma unroll
   for (int k = 0; k < LPT; ++k) {
     const int ci = tid + 256 * k;
@@ -463,20 +478,21 @@ __global__ __launch_bounds__(256) void prep_v_kernel(PrepArgs args) {
     if (tid < 4)
       args.g[(int64_t)bh * 4 + tid] =
           tid < 3 ? nvfp4_scale_global(tid == 2 ? st_g : st[tid]) : __uint_as_float(args.tag);
-    if (tid == 2 || tid == 3) args.stats[(int64_t)bh * (4 + D) + tid] = tid == 2 ? st_g : 0u;
+    if (args.vparts && (tid == 2 || tid == 3)) args.stats[(int64_t)bh * (4 + D) + tid] = tid == 2 ? st_g : 0u;
   }
 }
 
 template <int D, typename T>
-void launch_prep_t(const PrepArgs& args, hipStream_t stream) {
+void launch_prep_t(const PrepArgs& a, hipStream_t stream) {
+  PrepArgs args = a;
   const int BH = args.B * args.H;
-  const bool small = (int64_t)args.N * D * (int64_t)sizeof(T) <= kVstatSmall;
-  if (!small) {
-    hipLaunchKernelGGL(zero_vstats_kernel, dim3(BH), dim3(D), 0, stream, args.stats, args.d);
+  args.vparts = (int64_t)args.N * D * (int64_t)sizeof(T) <= kVstatSmall ? kVstatParts : 0;
+  if (!args.vparts) {
+    hipLaunchKernelGGL(zero_vstats_kernel, dim3(BH), dim3(64), 0, stream, args.stats, args.d);
     hipLaunchKernelGGL((prep_vstats_kernel<D, T>), dim3((args.N + kVstatRows - 1) / kVstatRows, BH), dim3(256), 0,
                        stream, args);
   }
-  hipLaunchKernelGGL((prep_qk_kernel<D, T>), dim3(args.R + (small ? kVstatParts : 0), BH, 2), dim3(256), 0, stream, args);
+  hipLaunchKernelGGL((prep_qk_kernel<D, T>), dim3(args.R + args.vparts, BH, 2), dim3(256), 0, stream, args);
   hipLaunchKernelGGL((prep_v_kernel<D, T>), dim3(args.R, BH), dim3(256), 0, stream, args);
 }
 

@@ -177,7 +177,8 @@ int32_t da2_ws_draft_offsets(const da2_problem* p, int64_t* offsets7);
  * a*R+b (head) or b (row); ranks [0,T16) -> 16, the next T8 -> 8, the next
  * T4 -> 4, others -> 0. The hot path runs with num16 = 0.
  *   A      device float32 [B,H,R,R] (e.g. from da2_draft_map)
- *   cls    device out, uint8 [B,H,R,R] in {0,4,8,16}
+ *   cls    device out, uint8 [B,H,R,R] in {0,4,8,16}; scratch of the call until
+ *          the classes are written
  *   lists  device out, lists_bytes (see da2_lists_offsets)
  * Errors: INVALID_ARG if den <= 0, a budget < 0, num16+num8+num4 > den, or
  * head scope with R*R >= 2^22; UNSUPPORTED for row scope with R > 8192. */

@@ -49,8 +49,10 @@ __device__ inline uint64_t rank_key(float a, uint32_t idx) {
 
 // Four consecutive scores; rows start at any multiple of 4 bytes.
 typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
-typedef uint32_t u32u1 __attribute__((aligned(1)));
-typedef uint32_t u32u2 __attribute__((aligned(2)));
+// Words stored over bytes and 16-bit entries, and read back over the latter.
+typedef uint32_t u32u1 __attribute__((aligned(1), may_alias));
+typedef uint32_t u32u2 __attribute__((aligned(2), may_alias));
+typedef uint32_t u32a __attribute__((may_alias));
 
 // ---- head scope: threshold keys ------------------------------------------------
 constexpr int kBins = 1024;            // bins of a key range
@@ -825,7 +827,7 @@ __device__ inline void write_row(const RankArgs& args, int64_t row, const uint32
   const int n = (int)(n4 + n8 + n16);
   for (int i = 2 * lane; i < n; i += 128) {
     if (i + 1 < n)
-      *reinterpret_cast<u32u2*>(keys + i) = *reinterpret_cast<const uint32_t*>(keys_l + i);
+      *reinterpret_cast<u32u2*>(keys + i) = *reinterpret_cast<const u32a*>(keys_l + i);
     else
       keys[i] = keys_l[i];
   }

@@ -42,9 +42,9 @@ namespace da2 {
 // launch take a part of the channels each, over all tokens, and store their
 // maxima, which saves both launches (whole layer: 512 tokens x 2 heads 48 -> 42
 // us, 4,255 x 12, d = 64, 105 -> 103; at that size the parts take as long as
-// prep_qk itself), and prep_v derives the head's max|V| from the channels' (in
-// large heads that costs each of prep_v's workgroups more than the atomic: 130.6
-// against 132.7 us for the call on the 12 heads).
+// prep_qk itself), and prep_v derives the head's max|V| from the channels'. Large
+// heads accumulate it with one more atomic; deriving it there as well measured
+// the same (125.7 and 125.2 us for the call in one process).
 __global__ void zero_vstats_kernel(uint32_t* stats, int d) {
   uint32_t* s = stats + (int64_t)blockIdx.x * (4 + d);
   for (int i = 2 + threadIdx.x; i < 4 + d; i += blockDim.x) s[i] = 0u;

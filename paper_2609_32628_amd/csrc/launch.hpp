@@ -70,7 +70,6 @@ struct PrepArgs {
   int with16;
   int fmt4;
   uint32_t tag;  // ops_tag(fmt4, with16), written into word 3 of each head's g entry
-  int vparts;    // extra workgroups per head that take V's statistics in the Q/K launch (0: own launches)
 };
 
 struct AttnArgs {

@@ -43,8 +43,7 @@ namespace da2 {
 // maxima, which saves both launches (whole layer: 512 tokens x 2 heads 48 -> 42
 // us, 4,255 x 12, d = 64, 105 -> 103; at that size the parts take as long as
 // prep_qk itself), and prep_v derives the head's max|V| from the channels'. Large
-// heads accumulate it with one more atomic; deriving it there as well measured
-// the same (125.7 and 125.2 us for the call in one process).
+// heads accumulate it with one more atomic.
 __global__ void zero_vstats_kernel(uint32_t* stats, int d) {
   uint32_t* s = stats + (int64_t)blockIdx.x * (4 + d);
   for (int i = 2 + threadIdx.x; i < 4 + d; i += blockDim.x) s[i] = 0u;
@@ -229,7 +228,10 @@ __device__ inline float mx_inv_scale(int k) { return __uint_as_float(static_cast
 constexpr int mx_block_bytes(int D) { return 1024 * (D / 32 + 1); }
 
 // ---- Q and K ----------------------------------------------------------------
-template <int D, typename T>
+// PARTS: a small head's launch, with extra workgroups for V's statistics (a
+// separate instantiation, because their loads in flight take 16 registers more
+// than the encoding and cost large heads two waves per SIMD).
+template <int D, typename T, bool PARTS>
 __global__ __launch_bounds__(256) void prep_qk_kernel(PrepArgs args) {
   constexpr int EPC = 16 / sizeof(T);
   constexpr int NG = D / 16;                // 16-channel groups per slot
@@ -238,9 +240,11 @@ __global__ __launch_bounds__(256) void prep_qk_kernel(PrepArgs args) {
   __shared__ float s_red[4];
   const int a = blockIdx.x, bh = blockIdx.y, which = blockIdx.z;  // which: 0 = Q, 1 = K
   const int b = bh / args.H, h = bh % args.H, R = args.R, tid = threadIdx.x;
-  if (a >= R) {  // extra workgroups of small heads
-    if (which == 0) vstats_part<D, T>(args, bh, a - R);
-    return;
+  if constexpr (PARTS) {
+    if (a >= R) {
+      if (which == 0) vstats_part<D, T>(args, bh, a - R);
+      return;
+    }
   }
   const Layout L = layout_view(args.layout, R, args.Npad);
   const int n = L.n_a[a];
@@ -344,7 +348,7 @@ __global__ __launch_bounds__(256) void prep_qk_kernel(PrepArgs args) {
 
 // ---- V ------------------------------------------------------------------------
 
-template <int D, typename T>
+template <int D, typename T, bool PARTS>
 __global__ __launch_bounds__(256) void prep_v_kernel(PrepArgs args) {
   constexpr int EPC = 16 / sizeof(T);
   constexpr int CPR = D / EPC;
@@ -377,8 +381,8 @@ __global__ __launch_bounds__(256) void prep_v_kernel(PrepArgs args) {
   // their bits order like they do)
   const int p = tid % (D / 2), sg = tid / (D / 2);
   const uint32_t st_c0 = st[4 + p], st_c1 = st[4 + p + D / 2];
-  uint32_t st_g = st[args.vparts ? 4 + (tid & 63) : 2];
-  if (args.vparts) {
+  uint32_t st_g = st[PARTS ? 4 + (tid & 63) : 2];
+  if constexpr (PARTS) {
     if (D == 128) st_g = max(st_g, st[68 + (tid & 63)]);
     for (int o = 32; o > 0; o >>= 1) st_g = max(st_g, (uint32_t)__shfl_xor(st_g, o, 64));
   }
@@ -477,23 +481,24 @@ __global__ __launch_bounds__(256) void prep_v_kernel(PrepArgs args) {
     if (tid < D) args.dV[(int64_t)bh * D + tid] = __fdiv_rn(__uint_as_float(st[4 + tid]), 2.25f);
     if (tid < 4)
       args.g[(int64_t)bh * 4 + tid] =
-          tid < 3 ? nvfp4_scale_global(tid == 2 ? st_g : st[tid]) : __uint_as_float(args.tag);
-    if (args.vparts && (tid == 2 || tid == 3)) args.stats[(int64_t)bh * (4 + D) + tid] = tid == 2 ? st_g : 0u;
+          tid < 3 ? nvfp4_scale_global(PARTS && tid == 2 ? st_g : st[tid]) : __uint_as_float(args.tag);
+    if (PARTS && (tid == 2 || tid == 3)) args.stats[(int64_t)bh * (4 + D) + tid] = tid == 2 ? st_g : 0u;
   }
 }
 
 template <int D, typename T>
-void launch_prep_t(const PrepArgs& a, hipStream_t stream) {
-  PrepArgs args = a;
+void launch_prep_t(const PrepArgs& args, hipStream_t stream) {
   const int BH = args.B * args.H;
-  args.vparts = (int64_t)args.N * D * (int64_t)sizeof(T) <= kVstatSmall ? kVstatParts : 0;
-  if (!args.vparts) {
-    hipLaunchKernelGGL(zero_vstats_kernel, dim3(BH), dim3(64), 0, stream, args.stats, args.d);
-    hipLaunchKernelGGL((prep_vstats_kernel<D, T>), dim3((args.N + kVstatRows - 1) / kVstatRows, BH), dim3(256), 0,
-                       stream, args);
+  if ((int64_t)args.N * D * (int64_t)sizeof(T) <= kVstatSmall) {
+    hipLaunchKernelGGL((prep_qk_kernel<D, T, true>), dim3(args.R + kVstatParts, BH, 2), dim3(256), 0, stream, args);
+    hipLaunchKernelGGL((prep_v_kernel<D, T, true>), dim3(args.R, BH), dim3(256), 0, stream, args);
+    return;
   }
-  hipLaunchKernelGGL((prep_qk_kernel<D, T>), dim3(args.R + args.vparts, BH, 2), dim3(256), 0, stream, args);
-  hipLaunchKernelGGL((prep_v_kernel<D, T>), dim3(args.R, BH), dim3(256), 0, stream, args);
+  hipLaunchKernelGGL(zero_vstats_kernel, dim3(BH), dim3(64), 0, stream, args.stats, args.d);
+  hipLaunchKernelGGL((prep_vstats_kernel<D, T>), dim3((args.N + kVstatRows - 1) / kVstatRows, BH), dim3(256), 0,
+                     stream, args);
+  hipLaunchKernelGGL((prep_qk_kernel<D, T, false>), dim3(args.R, BH, 2), dim3(256), 0, stream, args);
+  hipLaunchKernelGGL((prep_v_kernel<D, T, false>), dim3(args.R, BH), dim3(256), 0, stream, args);
 }
 
 hipError_t launch_prep(const PrepArgs& args, hipStream_t stream) {

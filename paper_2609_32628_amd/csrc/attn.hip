@@ -130,9 +130,11 @@ __device__ inline float e4m3_round_hw(float a) {
   return __builtin_amdgcn_cvt_f32_fp8(__builtin_amdgcn_cvt_pk_fp8_f32(a, 0.0f, __float_as_int(a), false), 0);
 }
 __device__ inline void fp4_setup(Fp4Group& G, float gmax, float c, float mn) {
+  // mn is a rounded product and the fused one is not, so pmax exceeds 1 by up to
+  // half an ulp of mn in the exponent: without the clamp 448 pmax passes 464 from
+  // |mn| = 2^20 on (constant Q = K = 344), where the conversion returns NaN
   const float pmax = exp2_fast(__builtin_fmaf(gmax, c, -mn));
-  // pmax exceeds 1 by a few ulp at most, and everything below 464 rounds to 448
-  const float sigma = e4m3_round_hw(448.0f * pmax);
+  const float sigma = e4m3_round_hw(fminf(448.0f * pmax, 448.0f));
   const float sg = fmaxf(sigma, kE4m3Min);
   G.off = (kLog2_2688 - __builtin_amdgcn_logf(sg)) - mn;
   G.scale = sg * (1.0f / 2688.0f);

@@ -3,10 +3,13 @@ change: each case is small and compared with the oracle at the same bars as
 the stage and end-to-end parity tests."""
 from dataclasses import replace
 
+import numpy as np
 import pytest
+import torch
 
-from gpu_harness import SMALL, inputs
-from test_gpu_parity import _check_end_to_end, _gpu  # noqa: F401  (_gpu: module fixture)
+from gpu_harness import SMALL, inputs, log
+from oracle import pipeline
+from test_gpu_parity import _check_end_to_end, _gpu, _run_gpu  # noqa: F401  (_gpu: module fixture)
 from test_gpu_parity import test_draft_map_row_lengths as _check_draft_map, test_prep_operands as _check_operands
 
 pytestmark = pytest.mark.gpu
@@ -48,3 +51,29 @@ def test_rows_dealt_to_xcds(B, H, T):
     none, two or more parts: every row is computed."""
     w = replace(SMALL, name=f"deal-{B}x{H}x{T}", B=B, H=H, T=T, Hg=8, Wg=8, scope="head")
     _check_end_to_end(w, *inputs(w))
+
+
+# Relative error of an output whose key logits are all equal: the float32
+# exponent of a weight may be off by an ulp of the running maximum (half of it
+# from the maximum, half from the fused offset), and the denominator sums what
+# the quantizer of the phase then rounds or saturates.
+def _equal_logits_bound(w, value):
+    x = np.float32(value * value * np.sqrt(w.d) * np.log2(np.e))
+    return 2.0 ** float(np.spacing(x)) - 1.0
+
+
+@pytest.mark.parametrize("d,value", [(64, 344.0), (64, 500.0), (128, 250.0), (128, 344.0), (128, 352.0)])
+def test_large_equal_logits_nvfp4(d, value):
+    """Constant Q and K whose logits reach 2^20 in log2 units: a group's scaled
+    maximum may pass the largest E4M3 value and has to saturate, not to become
+    NaN."""
+    w = replace(SMALL, name=f"equal-{value:g}-d{d}", B=1, d=d, budgets=(0, 100, 100), scope="row")
+    Q, K, V = inputs(w)
+    Q, K = np.full_like(Q, value), np.full_like(K, value)
+    O = _run_gpu(w, Q, K, V)[2].cpu().numpy().reshape(w.H, w.N, d)
+    _, outs = pipeline.run(w, Q, K, V)
+    for h, o in enumerate(outs):
+        assert np.isfinite(O[h]).all(), (h, np.isnan(O[h]).any(axis=-1).sum())
+        rel = np.abs(O[h] - o["O"]).max() / np.abs(o["O"]).max()
+        log(f"  head {h}: rel {rel:.2e}, bound {_equal_logits_bound(w, value):.2e}")
+        assert rel <= _equal_logits_bound(w, value) + 5e-3

@@ -273,6 +273,18 @@ __device__ inline void mask_tail(f32x16 (&S)[2], int nb, int slot0, int slot1, i
   S[0] = __builtin_amdgcn_mfma_f32_32x32x8f16(m0, one, S[0], 0, 0, 0);
   S[1] = __builtin_amdgcn_mfma_f32_32x32x8f16(m1, one, S[1], 0, 0, 0);
 }
+// The same by bit selects, for logits that may be NaN on padding slots (adding
+// -inf keeps a NaN). Register i of tile j holds slot 32 j + 16 g + i.
+__device__ inline void mask_tail_select(f32x16 (&S)[2], int nb, int g) {
+#pragma unroll
+  for (int j = 0; j < 2; ++j)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      uint32_t t = static_cast<uint32_t>((nb - 32 * j - 16 * g - 1 - i) >> 31);  // all ones: masked
+      asm("" : "+v"(t));  // no compare masks: 32 of them do not fit the scalar registers
+      S[j][i] = __uint_as_float((t & 0xFF800000u) | (~t & __float_as_uint(S[j][i])));
+    }
+}
 // Slot of key row r of tile 0 (tile 1: 32 more; in the MXFP4 key order 16 more).
 __device__ inline int row_slot(int r) { return 16 * ((r >> 2) & 1) + 4 * (r >> 3) + (r & 3); }
 __device__ inline int row_slot_mx(int r) { return 32 * ((r >> 2) & 1) + 4 * (r >> 3) + (r & 3); }
@@ -1077,6 +1089,18 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(2))) void m
     const f16x8* Qa = reinterpret_cast<const f16x8*>(args.Q16) + (blk0 + a) * (kCap * D / 8);
 #pragma unroll
     for (int s = 0; s < NS16; ++s) Qf[s] = Qa[(qt * NS16 + s) * 64 + lane];
+    // A query value beyond the fp16 range is infinite and its product with the
+    // zeros of a padding slot NaN, although the query's output may be finite
+    // (logits of -inf in this phase, finite ones in another): such a tile masks
+    // by selects. An all-ones exponent carries into the sign bit.
+    uint32_t top = 0;
+#pragma unroll
+    for (int s = 0; s < NS16; ++s) {
+      const i32x4 x = __builtin_bit_cast(i32x4, Qf[s]);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) top |= (static_cast<uint32_t>(x[e]) & 0x7C007C00u) + 0x04000400u;
+    }
+    const bool unbounded = __ballot((top & 0x80008000u) != 0) != 0;
     f16x8 P[4];
     float alpha = 1.0f;
     typedef f32x16 SA[2];
@@ -1092,7 +1116,12 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(2))) void m
     // Region 1: logits of the next block with the maxima and the first
     // group's weights of the current block (four pieces over the stages).
     auto region1 = [&]<bool MASK>(SA& Sc, SA& Sn, int nb) {
-      if constexpr (MASK) mask_tail(Sc, nb, row_slot(r), row_slot(r) + 32, lane);
+      if constexpr (MASK) {
+        if (__builtin_expect(unbounded, 0))
+          mask_tail_select(Sc, nb, g);
+        else
+          mask_tail(Sc, nb, row_slot(r), row_slot(r) + 32, lane);
+      }
       f16x8 k0 = sK[lane], k1 = sK[NS16 * 64 + lane];
       constexpr int NP = 4;
       sum0 = 0.0f;

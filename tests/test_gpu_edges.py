@@ -77,3 +77,17 @@ def test_large_equal_logits_nvfp4(d, value):
         rel = np.abs(O[h] - o["O"]).max() / np.abs(o["O"]).max()
         log(f"  head {h}: rel {rel:.2e}, bound {_equal_logits_bound(w, value):.2e}")
         assert rel <= _equal_logits_bound(w, value) + 5e-3
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("dtype", ["fp32", "bf16"])
+def test_queries_beyond_half_precision(d, dtype):
+    """Queries with a value of -70,144 (infinite in fp16) in a channel where
+    every key is positive: their 16-bit logits are -inf, on partial blocks too,
+    and the 4-bit and 8-bit pairs alone make the output."""
+    w = replace(SMALL, name=f"half-inf-{dtype}-d{d}", B=1, d=d, dtype=dtype, num16=30, budgets=(30, 40, 100),
+                scope="row")
+    Q, K, V = inputs(w)
+    Q[:, :, ::7, 0] = -70144.0
+    K[..., 0] = 2.0 ** -6
+    _check_end_to_end(w, Q, K, V)

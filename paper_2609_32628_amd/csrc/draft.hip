@@ -339,8 +339,8 @@ __global__ __launch_bounds__(256) void draft_softmax_kernel(DraftArgs args) {
 }
 
 // Short rows (R <= 64 KT): one workgroup owns 16 rows of a head, both branches
-// and every column, so the two logit tiles never leave its registers and the
-// row softmaxes follow in the same launch. Wave w holds the column tiles
+// and every column, so the row softmaxes follow in the same launch and read the
+// logits from registers (they are stored for the workspace only). Wave w holds the column tiles
 // w, w + 4, ... (KT of them); row statistics are reduced over the 16 lanes of
 // an accumulator row, then over the waves through LDS. At these sizes a
 // 128x160 tile per workgroup leaves the chip idle and its one wave round is
@@ -419,17 +419,23 @@ __global__ __launch_bounds__(256) void draft_rows_kernel(DraftArgs args) {
   };
   double m[2][4], z[2][4];
 #pragma unroll
-  for (int br = 0; br < 2; ++br)
+  for (int br = 0; br < 2; ++br) {
+    // the workspace holds the logits of every row length
+    double* S = (br == 0 ? args.S1 : args.S2) + (int64_t)bh * R * R;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       m[br][e] = -INFINITY;
+      const int row = r0 + q + 4 * e;
 #pragma unroll
       for (int k = 0; k < KT; ++k) {
-        const bool in = 16 * (wave + 4 * k) + li < R;
+        const int col = 16 * (wave + 4 * k) + li;
+        const bool in = col < R;
         acc[br][k][e] = in ? acc[br][k][e] * rsqd : -INFINITY;
+        if (in && row < R) S[row * R + col] = acc[br][k][e];
         m[br][e] = fmax(m[br][e], acc[br][k][e]);
       }
     }
+  }
   row_reduce(m, [](double x, double y) { return fmax(x, y); });
 #pragma unroll
   for (int br = 0; br < 2; ++br)

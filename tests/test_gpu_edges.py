@@ -7,8 +7,9 @@ import numpy as np
 import pytest
 import torch
 
-from gpu_harness import SMALL, inputs, log
+from gpu_harness import SMALL, inputs, log, problem_of, to_device
 from oracle import pipeline
+from paper_2609_32628_amd import api
 from test_gpu_parity import _check_end_to_end, _gpu, _run_gpu  # noqa: F401  (_gpu: module fixture)
 from test_gpu_parity import test_draft_map_row_lengths as _check_draft_map, test_prep_operands as _check_operands
 
@@ -33,6 +34,27 @@ def test_draft_map_short_rows(R, d):
     """R one-block frames: the edges of the short-row kernel's column tiles and
     the first length that takes the tiled kernel."""
     _check_draft_map(replace(SMALL, name=f"draft-R{R}-d{d}", B=1, H=2, d=d, T=R, Hg=7, Wg=8))
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("R", [1, 17, 65, 129, 256, 257])
+def test_draft_workspace_holds_the_logits(R, d):
+    """S_avg and S_max of da2_ws_draft_offsets are the logits of the pooled
+    descriptors beside them, at both kernels' row lengths."""
+    w = replace(SMALL, name=f"draft-ws-R{R}-d{d}", B=1, H=2, d=d, T=R, Hg=7, Wg=8)
+    Q, K, _ = inputs(w)
+    p = problem_of(w)
+    buf = api.alloc(p, w.scope)
+    buf.ws_draft.fill_(0xA5)
+    api.da2_draft_map(to_device(Q, w), to_device(K, w), buf.layout, p, w.lam, buf.A, buf.stats, buf.ws_draft)
+    torch.cuda.synchronize()
+    ws, off = buf.ws_draft.cpu().numpy(), api.da2_ws_draft_offsets(p)
+    at = [ws[off[i]:off[i] + 16 * R * n].view(np.float64).reshape(2, R, n) for i, n in enumerate([d] * 4 + [R] * 2)]
+    for i in (0, 1):   # average and maximum pooling
+        q, k, S = at[i], at[2 + i].transpose(0, 2, 1), at[4 + i]
+        # float64 sums of d products in any order, scaled by a rounded 1 / sqrt d
+        bound = (d + 4) * 2.0 ** -53 * (np.abs(q) @ np.abs(k)) / np.sqrt(d)
+        assert (np.abs(S - q @ k / np.sqrt(d)) <= 2 * bound).all()
 
 
 @pytest.mark.parametrize("dtype,d,n", [("fp32", 128, 2048), ("fp32", 128, 2049), ("fp32", 64, 4096), ("fp32", 64, 4097),

@@ -340,16 +340,14 @@ __global__ __launch_bounds__(256) void draft_softmax_kernel(DraftArgs args) {
 
 // Short rows (R <= 64 KT): one workgroup owns 16 rows of a head, both branches
 // and every column, so the row softmaxes follow in the same launch and read the
-// logits from registers (they are stored for the workspace only). Wave w holds the column tiles
-// w, w + 4, ... (KT of them); row statistics are reduced over the 16 lanes of
-// an accumulator row, then over the waves through LDS. At these sizes a
-// 128x160 tile per workgroup leaves the chip idle and its one wave round is
-// the time: 12.8 + 4 us for the two launches at R = 8 x 2 heads, 14 + 5 us at
+// logits from registers (they are stored for the workspace only). Wave w holds
+// the column tiles w, w + 4, ... (KT of them); row statistics are reduced over
+// the 16 lanes of an accumulator row, then over the waves through LDS. At these
+// sizes a 128x160 tile per workgroup leaves the chip idle and its one wave round
+// is the time: 12.8 + 4 us for the two launches at R = 8 x 2 heads, 14 + 5 us at
 // R = 70 x 12 heads. Beyond 256 columns a wave would need more than 64
 // accumulator registers, every key operand still feeds one product only, and
-// the tiled kernel wins. Whole draft_map call, two launches against this:
-// R = 8 x 2 heads 19.6 -> 12.8 us, 75 x 12 (d = 128) 35 -> 24, 200 x 12
-// 47 -> 41, 200 x 40 108 -> 103.
+// the tiled kernel wins; use_rows() has the limits on the number of workgroups.
 template <int D, int KT>
 __global__ __launch_bounds__(256) void draft_rows_kernel(DraftArgs args) {
   constexpr int d = D, NT = d / 8;
@@ -472,7 +470,22 @@ __global__ __launch_bounds__(256) void draft_rows_kernel(DraftArgs args) {
   }
 }
 
-constexpr int kShortRow = 256;
+// Whether the short-row kernel is the faster one. Its workgroups each read all
+// keys of their head, so beyond about one (KT = 4) or two of them per compute
+// unit the tiled kernel's reuse of its operands wins. Whole call, tiled against
+// short rows, us (d = 64 / d = 128; workgroups):
+//   R = 8 x 2 heads  19.3 / 28.2, 13.6 / 13.4 (2)     R = 40 x 80  29.4 / 45.2, 21.5 / 31.5 (240)
+//   R = 75 x 12      23.2 / 34.3, 17.9 / 24.2 (60)    R = 75 x 80  39.3 / 62.1, 36.0 / 56.9 (400)
+//   R = 128 x 40     38.8 / 59.0, 37.2 / 58.5 (320)   R = 100 x 80 46.7 / 80.0, 47.5 / 84.9 (560)
+//   R = 160 x 24     35.2 / 52.3, 31.5 / 46.7 (240)   R = 192 x 24 38.8 / 57.9, 42.9 / 66.4 (288)
+//   R = 256 x 12     34.0 / 49.4, 32.5 / 48.0 (192)   R = 256 x 40 70.9 / 127.5, 73.4 / 134.3 (640)
+// (R = 192 x 40, 480 workgroups: 60.4 / 100.8, 51.0 / 88.1; it stays with the
+// tiled kernel, whose time the head counts around it share.) Up to 48 blocks a
+// tile is mostly padding and the short rows win at every head count.
+inline bool use_rows(int R, int BH) {
+  const int64_t groups = (int64_t)((R + 15) / 16) * BH;
+  return R <= 48 || (R <= 128 ? groups <= 512 : R <= 256 && groups <= 256);
+}
 
 template <int D>
 void launch_rows(const DraftArgs& args, hipStream_t stream) {
@@ -499,7 +512,7 @@ hipError_t launch_draft(const DraftArgs& args, hipStream_t stream) {
     else
       hipLaunchKernelGGL((draft_pool_kernel<64, float>), pool_grid, dim3(256), 0, stream, args);
   }
-  if (args.R <= kShortRow) {
+  if (use_rows(args.R, BH)) {
     if (args.d == 128)
       launch_rows<128>(args, stream);
     else

@@ -37,11 +37,13 @@ def test_draft_map_short_rows(R, d):
 
 
 @pytest.mark.parametrize("d", [64, 128])
-@pytest.mark.parametrize("R", [1, 17, 65, 129, 256, 257])
-def test_draft_workspace_holds_the_logits(R, d):
+@pytest.mark.parametrize("R,H", [(1, 2), (17, 2), (65, 2), (128, 2), (129, 2), (256, 2), (257, 2), (48, 172),
+                                 (49, 128), (49, 129), (241, 16), (241, 17)])
+def test_draft_workspace_holds_the_logits(R, H, d):
     """S_avg and S_max of da2_ws_draft_offsets are the logits of the pooled
-    descriptors beside them, at both kernels' row lengths."""
-    w = replace(SMALL, name=f"draft-ws-R{R}-d{d}", B=1, H=2, d=d, T=R, Hg=7, Wg=8)
+    descriptors beside them, for both kernels: their row lengths and the numbers
+    of workgroups at which one takes over from the other."""
+    w = replace(SMALL, name=f"draft-ws-R{R}-h{H}-d{d}", B=1, H=H, d=d, T=R, Hg=1, Wg=3)
     Q, K, _ = inputs(w)
     p = problem_of(w)
     buf = api.alloc(p, w.scope)
@@ -49,12 +51,16 @@ def test_draft_workspace_holds_the_logits(R, d):
     api.da2_draft_map(to_device(Q, w), to_device(K, w), buf.layout, p, w.lam, buf.A, buf.stats, buf.ws_draft)
     torch.cuda.synchronize()
     ws, off = buf.ws_draft.cpu().numpy(), api.da2_ws_draft_offsets(p)
-    at = [ws[off[i]:off[i] + 16 * R * n].view(np.float64).reshape(2, R, n) for i, n in enumerate([d] * 4 + [R] * 2)]
+    at = [ws[off[i]:off[i] + 8 * H * R * n].view(np.float64).reshape(H, R, n) for i, n in enumerate([d] * 4 + [R] * 2)]
     for i in (0, 1):   # average and maximum pooling
         q, k, S = at[i], at[2 + i].transpose(0, 2, 1), at[4 + i]
         # float64 sums of d products in any order, scaled by a rounded 1 / sqrt d
         bound = (d + 4) * 2.0 ** -53 * (np.abs(q) @ np.abs(k)) / np.sqrt(d)
         assert (np.abs(S - q @ k / np.sqrt(d)) <= 2 * bound).all()
+    # and the map is their softmaxes' mixture
+    e = [np.exp(S - S.max(axis=2, keepdims=True)) for S in at[4:]]
+    A = (1 - w.lam) * e[0] / e[0].sum(axis=2, keepdims=True) + w.lam * e[1] / e[1].sum(axis=2, keepdims=True)
+    np.testing.assert_allclose(buf.A.cpu().numpy()[0], A, rtol=2.0 ** -23, atol=1e-37)
 
 
 @pytest.mark.parametrize("dtype,d,n", [("fp32", 128, 2048), ("fp32", 128, 2049), ("fp32", 64, 4096), ("fp32", 64, 4097),

@@ -875,19 +875,20 @@ __global__ __launch_bounds__(256) void rank_rows_head_kernel(RankArgs args) {
 #pragma unroll
   for (int st = 0; st < ST; ++st) load_scores(A, 256 * st + 4 * lane, R, x[st]);
   // scores at or above from[t] are in; in the threshold's own row, of the
-  // scores equal to it those at columns up to last[t]
-  uint32_t from[kCuts];
+  // scores equal to it those at columns up to last[t] (so, too, where no image
+  // lies above the threshold's, that of a NaN of all ones)
+  uint32_t from[kCuts], t32[kCuts];
   int last[kCuts], empty = 0;
   bool own = false;
 #pragma unroll
   for (int t = 0; t < kCuts; ++t) {
     const uint64_t thr = args.thr[bh * kCuts + t];
     empty += thr == kNone;
-    const uint32_t t32 = (uint32_t)(thr >> kIdxBits);
+    t32[t] = (uint32_t)(thr >> kIdxBits);
     const int64_t c = (int64_t)(kIdxMask - ((uint32_t)thr & kIdxMask)) - (int64_t)a * R;
     last[t] = (int)(c < -1 ? -1 : (c > R ? R : c));
-    own = own || (thr != kNone && last[t] >= 0 && last[t] < R - 1);
-    from[t] = last[t] < 0 && t32 != 0xFFFFFFFFu ? t32 + 1u : t32;
+    own = own || (thr != kNone && last[t] < R - 1 && (last[t] >= 0 || t32[t] == 0xFFFFFFFFu));
+    from[t] = last[t] < 0 ? t32[t] + 1u : t32[t];
   }
   uint32_t xs[ST];
   // E: empty cuts (the first ones, since the cuts are cumulative)
@@ -902,7 +903,7 @@ __global__ __launch_bounds__(256) void rank_rows_head_kernel(RankArgs args) {
         uint32_t r = 0;
 #pragma unroll
         for (int t = E; t < kCuts; ++t)
-          r += s >= from[t] && !(OWN && s == from[t] && b + e > last[t] && last[t] >= 0) ? 1u : 0u;
+          r += (OWN ? s > t32[t] || (s == t32[t] && b + e <= last[t]) : s >= from[t]) ? 1u : 0u;
         xs[st] |= r << (8 * e);
       }
       if (256 * st + 256 > R) {  // the row's last step: no class beyond its end

@@ -48,6 +48,8 @@ def _scores(kind, R, seed):
     elif kind == "signed":
         A = rng.standard_normal((R, R)).astype(np.float32)
         A[0, :min(R, 3)] = [np.inf, -np.inf, 1e-42][:min(R, 3)]
+    elif kind == "nan":       # the NaN whose bits order above every other value's, in a third of the places
+        A[rng.random((R, R)) < 0.3] = np.array(0x7FFFFFFF, np.uint32).view(np.float32)
     elif kind == "unsampled-high":   # every sampled score is below every other one: all brackets miss
         A.reshape(-1)[_sampled(R * R)] = 1e-20
     elif kind == "unsampled-inside":  # all other scores lie inside the brackets: the gathered keys do not fit
@@ -71,7 +73,7 @@ def _check(R, scope, kind, budgets, H=2):
     keys, counts, order = lists_of(buf, p)
     assert np.array_equal(np.sort(order), np.arange(H * R))
     for h in range(H):
-        want = orank.rank_head(A[h], num8, num4, den, scope, num16=num16)
+        want = orank.rank_head(np.where(np.isnan(A[h]), np.float32(np.inf), A[h]), num8, num4, den, scope, num16=num16)
         assert np.array_equal(cls[h], want), h
         for a in range(R):
             row = h * R + a
@@ -98,6 +100,13 @@ def test_distributions(R, scope, kind):
         pytest.skip("this head is selected without a sample")
     for budgets in (BUDGETS, (0, 10, 30, 100), (0, 0, 50, 100), (1, 998, 0, 1000), (100, 0, 0, 100), (0, 0, 0, 100)):
         _check(R, scope, kind, budgets, H=1)
+
+
+@pytest.mark.parametrize("R,scope", [(20, "head"), (200, "head"), (600, "head"), (200, "row")])
+def test_nan_scores(R, scope):
+    """Every threshold among equal scores of the largest image, and one below."""
+    for budgets in ((5, 10, 10, 100), (15, 10, 30, 100)):
+        _check(R, scope, "nan", budgets, H=1)
 
 
 @pytest.mark.parametrize("R,scope", [(2047, "head"), (2048, "row"), (2049, "row")])

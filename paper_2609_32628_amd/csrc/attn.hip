@@ -968,6 +968,16 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(2))) void m
 #pragma unroll
     for (int s = 0; s < NS32; ++s) Qf[s] = Qa[(qt * NS32 + s) * 64 + lane];
     const float c8a = args.dQ[blk0 + a] * kLog2e * rsqd;
+    // A weight's exponent fuses the exact product S cb, while the running maximum
+    // mn and the offset that subtracts it are rounded. Their error, an ulp of mn,
+    // may take the largest weight (448) past the 464 from which its conversion
+    // returns NaN; below |mn| = 2^19 it stays under 0.047 (log2 (464 / 448) is
+    // 0.0506). Where 127 x 127 x D codes at this block's and the head's largest
+    // scale (g holds max|K| / 2688, or 1 if that is zero) may exceed that, the
+    // offset is lowered by |mn| 2^-23, one to two ulps of mn (elsewhere by 0: the
+    // same bits), for weights and denominator alike.
+    const float dk_max = args.g[bh * 4 + 1] * (2688.0f / 127.0f) + 1e-7f;
+    const float slack = c8a * dk_max * (16129.0f * D) > 524288.0f ? -0x1p-23f : -0.0f;
     float alpha = 1.0f;
     typedef i32x16 SA[2];
     auto qk = [&](SA& S, const f16x8* sK0) {
@@ -1007,10 +1017,12 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(2))) void m
 #pragma unroll
         for (int piece = 0; piece < NP; ++piece) {
           if (piece * NS32 / NP != s) continue;
-          if (piece == 0)
-            off = kExpOffset - new_max(fmaxf(max16(sf[0]), max16(sf[1])), cb, m, l, alpha);
-          else
+          if (piece == 0) {
+            const float mn = new_max(fmaxf(max16(sf[0]), max16(sf[1])), cb, m, l, alpha);
+            off = __builtin_fmaf(fabsf(mn), slack, kExpOffset - mn);
+          } else {
             s0 = fp8_weights8<0>(sf[0], cb, off, w[0], w[1]);
+          }
         }
         fence();
         k0 = n0;

@@ -81,13 +81,27 @@ def test_rows_dealt_to_xcds(B, H, T):
     _check_end_to_end(w, *inputs(w))
 
 
-# Relative error of an output whose key logits are all equal: the float32
-# exponent of a weight may be off by an ulp of the running maximum (half of it
-# from the maximum, half from the fused offset), and the denominator sums what
-# the quantizer of the phase then rounds or saturates.
+# Relative error of an output whose key logits are all equal. 4-bit pairs: the
+# float32 exponent of a weight may be off by an ulp of the running maximum (half
+# of it from the maximum, half from the fused offset), and the denominator sums
+# what the quantizer then saturates. 8-bit pairs: weight and denominator share
+# that error, and the weight, 448 less up to three such ulps (2^-8 at 2^25), is
+# rounded to a normal E4M3 value.
 def _equal_logits_bound(w, value):
     x = np.float32(value * value * np.sqrt(w.d) * np.log2(np.e))
-    return 2.0 ** float(np.spacing(x)) - 1.0
+    return (2.0 ** float(np.spacing(x)) - 1.0 if w.budgets[1] else 2.0 ** -4) + 5e-3
+
+
+def _check_equal_logits(w, value, sign=1):
+    Q, K, V = inputs(w)
+    Q, K = np.full_like(Q, value), np.full_like(K, sign * value)
+    O = _run_gpu(w, Q, K, V)[2].cpu().numpy().reshape(w.H, w.N, w.d)
+    _, outs = pipeline.run(w, Q, K, V)
+    for h, o in enumerate(outs):
+        assert np.isfinite(O[h]).all(), (h, np.isnan(O[h]).any(axis=-1).sum())
+        rel = np.abs(O[h] - o["O"]).max() / np.abs(o["O"]).max()
+        log(f"  head {h}: rel {rel:.2e}, bound {_equal_logits_bound(w, value):.2e}")
+        assert rel <= _equal_logits_bound(w, value)
 
 
 @pytest.mark.parametrize("d,value", [(64, 344.0), (64, 500.0), (128, 250.0), (128, 344.0), (128, 352.0)])
@@ -95,16 +109,30 @@ def test_large_equal_logits_nvfp4(d, value):
     """Constant Q and K whose logits reach 2^20 in log2 units: a group's scaled
     maximum may pass the largest E4M3 value and has to saturate, not to become
     NaN."""
-    w = replace(SMALL, name=f"equal-{value:g}-d{d}", B=1, d=d, budgets=(0, 100, 100), scope="row")
+    _check_equal_logits(replace(SMALL, name=f"equal-{value:g}-d{d}", B=1, d=d, budgets=(0, 100, 100), scope="row"), value)
+
+
+@pytest.mark.parametrize("sign", [1, -1])
+@pytest.mark.parametrize("d,value", [(64, 250.0), (64, 1000.0), (64, 2000.0), (128, 215.0), (128, 500.0),
+                                     (128, 1000.0), (128, 1600.0)])
+def test_large_equal_logits_int8(d, value, sign):
+    """The same for 8-bit weights, of which the largest may pass 464; logits of
+    either sign."""
+    w = replace(SMALL, name=f"equal8-{value:g}-d{d}", B=1, d=d, budgets=(100, 0, 100), scope="row")
+    _check_equal_logits(w, value, sign)
+
+
+@pytest.mark.parametrize("fmt4,budgets", [("nvfp4", (0, 100, 100)), ("mxfp4", (0, 100, 100)), ("nvfp4", (100, 0, 100)),
+                                          ("nvfp4", (30, 70, 100)), ("mxfp4", (30, 70, 100))])
+@pytest.mark.parametrize("scale", [200.0, 400.0, 800.0, 3000.0])
+def test_large_logits_stay_finite(scale, fmt4, budgets):
+    """Different logits of up to 2^28 in log2 units, each phase and both."""
+    w = replace(SMALL, name=f"large-{scale:g}-{fmt4}", B=1, fmt4=fmt4, budgets=budgets, scope="row")
+    rng = np.random.default_rng(5)
     Q, K, V = inputs(w)
-    Q, K = np.full_like(Q, value), np.full_like(K, value)
-    O = _run_gpu(w, Q, K, V)[2].cpu().numpy().reshape(w.H, w.N, d)
-    _, outs = pipeline.run(w, Q, K, V)
-    for h, o in enumerate(outs):
-        assert np.isfinite(O[h]).all(), (h, np.isnan(O[h]).any(axis=-1).sum())
-        rel = np.abs(O[h] - o["O"]).max() / np.abs(o["O"]).max()
-        log(f"  head {h}: rel {rel:.2e}, bound {_equal_logits_bound(w, value):.2e}")
-        assert rel <= _equal_logits_bound(w, value) + 5e-3
+    Q = (scale * (1 + rng.standard_normal(Q.shape))).astype(Q.dtype)
+    K = (scale * (1 + 0.01 * rng.standard_normal(K.shape))).astype(K.dtype)
+    assert torch.isfinite(_run_gpu(w, Q, K, V)[2]).all()
 
 
 @pytest.mark.parametrize("d", [64, 128])

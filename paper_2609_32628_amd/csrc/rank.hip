@@ -26,6 +26,8 @@
 // Heads of up to kDirectKeys scores go straight to select. Row scope is one
 // launch: a wave per row selects, classifies and writes the lists (R <= 2048;
 // longer rows sort their keys in LDS).
+#include <algorithm>
+#include <cmath>
 #include <mutex>
 
 #include "common.hpp"
@@ -181,13 +183,13 @@ __global__ __launch_bounds__(256) void rank_sample_kernel(RankArgs args) {
 }
 
 // Bracket of one threshold key (workgroup (t, head)): a threshold of rank c lies
-// between the sample's ranks c S/M -+ (4 standard deviations of a random sample
-// + 4). The two bounds are narrowed by histograms: the first one is over the
+// between the sample's ranks c S/M -+ (sds standard deviations of a random sample
+// + 4), see bracket_sds. The two bounds are narrowed by histograms: the first one is over the
 // samples' scores and common to both (four copies, since neighbouring lanes
 // often hit one bin); in the second a sample's first bin tells which bound it
 // matters to; dense bins and ties take further ones over the keys. A bound is
 // done when its bin holds at most 16 samples, and widened to the bin's edge.
-__global__ __launch_bounds__(1024) void rank_bracket_kernel(RankArgs args) {
+__global__ __launch_bounds__(1024) void rank_bracket_kernel(RankArgs args, double sds) {
   constexpr int NB = 2;  // 0: the upper bound, 1: the lower one
   __shared__ uint32_t lh[4][kBins];
   __shared__ uint64_t s_lo[NB], s_hi[NB];
@@ -226,7 +228,7 @@ __global__ __launch_bounds__(1024) void rank_bracket_kernel(RankArgs args) {
   }
   if (tid < NB) {
     const double c = (double)args.cut[t], S = (double)(1 << lg), p = c / (double)M;
-    const double r = p * S, wd = 4.0 * sqrt(S * p * (1.0 - p)) + 4.0;
+    const double r = p * S, wd = sds * sqrt(S * p * (1.0 - p)) + 4.0;
     const double rr = tid == 0 ? floor(r - wd) : ceil(r + wd);
     s_open[tid] = rr >= 1.0 && rr <= S;
     s_k[tid] = (int64_t)rr;
@@ -1243,6 +1245,26 @@ hipError_t rank_scratch_address(void** out) {
   return hipSuccess;
 }
 
+// Half-width of the brackets in standard deviations of a sample's rank: 4 (a
+// bracket misses one threshold in 16,000), or what lets the gathered keys fill
+// 0.88 of the list, M/8 keys, if the brackets of all cuts are expected to hold
+// more (a bracket holds 23 samples on top: 4 and half a bin of 16 at either end).
+// That concerns small heads with three cuts in the middle of the ranks: 8,192
+// samples, 30/20/20% of the pairs, 3.2. With 4 their lists overflowed and select
+// read the scores: R = 362 x 12 heads 92 us, now 43; 0.88 leaves four
+// standard deviations of the number gathered.
+double bracket_sds(const RankArgs& args, int64_t M) {
+  const double S = (double)(1 << sample_bits(M));
+  double sd = 0.0, room = 0.88 * S / 8.0;
+  for (int t = 0; t < kCuts; ++t)
+    if (args.cut[t] > 0 && args.cut[t] < M) {
+      const double p = (double)args.cut[t] / (double)M;
+      sd += std::sqrt(S * p * (1.0 - p));
+      room -= 23.0;
+    }
+  return sd > 0.0 ? std::min(4.0, room / (2.0 * sd)) : 4.0;
+}
+
 template <int ST>
 void launch_rows(const RankArgs& args, hipStream_t stream) {
   const dim3 grid((unsigned)(((int64_t)args.B * args.H * args.R + 3) / 4));
@@ -1268,8 +1290,8 @@ hipError_t launch_rank(const RankArgs& args, hipStream_t stream) {
     const bool sampled = M > kDirectKeys;
     if (sampled) {
       hipLaunchKernelGGL(rank_sample_kernel, dim3((1 << sample_bits(M)) / 1024, BH), dim3(256), 0, stream, args);
-      hipLaunchKernelGGL(rank_bracket_kernel, dim3(kCuts, BH), dim3(1024), 0, stream, args);
-      // 8,192 keys per workgroup, more where that makes over 4,096 workgroups
+      hipLaunchKernelGGL(rank_bracket_kernel, dim3(kCuts, BH), dim3(1024), 0, stream, args, bracket_sds(args, M));
+      // 4,096 keys per workgroup, more where that makes over 4,096 workgroups
       const int64_t per = (BH * M / 4096 + 2047) / 2048 * 2048;
       const int chunk = (int)(per < 4096 ? 4096 : per);
       hipLaunchKernelGGL(rank_collect_kernel, dim3((unsigned)((M + chunk - 1) / chunk), BH), dim3(256), 0, stream, args,

@@ -13,7 +13,6 @@ from paper_2609_32628_amd import api
 pytestmark = pytest.mark.gpu
 
 
-
 @pytest.fixture(scope="module", autouse=True)
 def _gpu():
     assert torch.cuda.is_available(), "GPU tests need a GPU"
@@ -58,6 +57,35 @@ def _scores(kind, R, seed):
     return A
 
 
+def _routes(buf, A, h, H, cuts):
+    """How the head selection found each of head h's thresholds: "bracket" (from
+    the gathered keys), "missed" (the threshold lies outside its bracket) or
+    "overflow" (the gathered keys did not fit), from the brackets that the call
+    left in its workspace."""
+    M = A.size
+    ws = buf.ws_rank.cpu().numpy()
+    words = ws[:4 * H * 6144].view(np.uint32).reshape(H, 6144)[h]
+    at, size = 4 * H * 6144, -(-24 * H // 256) * 256           # then thresholds, lower and upper ends
+    lo, hi = (ws[at + i * size:at + i * size + 24 * H].view(np.uint64).reshape(H, 3)[h] for i in (1, 2))
+    u = (A.reshape(-1) + np.float32(0)).view(np.uint32)
+    img = np.where(u >> 31, ~u, u | np.uint32(0x80000000)).astype(np.uint64)
+    keys = (img << np.uint64(22)) | (np.uint64(2 ** 22 - 1) - np.arange(M, dtype=np.uint64))
+    inside, out = np.zeros(M, bool), []
+    for t, c in enumerate(cuts):
+        if not 0 < c < M:
+            out.append(None)
+            continue
+        mine = (keys >= lo[t]) & (keys <= hi[t])
+        inside |= mine
+        above = int((keys > hi[t]).sum())
+        assert words[32 * t] == above
+        out.append("bracket" if above < c <= above + mine.sum() else "missed")
+    # its part of the class map, up to seven bytes less for the alignment
+    fits = words[96] <= (M - (-h * M % 8)) // 8
+    assert words[96] == inside.sum()
+    return [r if r is None or fits else "overflow" for r in out]
+
+
 def _check(R, scope, kind, budgets, H=2):
     num16, num8, num4, den = budgets
     log(f"ranking R={R} {scope} {kind} {budgets}")
@@ -75,6 +103,10 @@ def _check(R, scope, kind, budgets, H=2):
     for h in range(H):
         want = orank.rank_head(np.where(np.isnan(A[h]), np.float32(np.inf), A[h]), num8, num4, den, scope, num16=num16)
         assert np.array_equal(cls[h], want), h
+        if scope == "head" and R >= 182 and budgets in ROUTES.get(kind, (None, ()))[1]:
+            routes = _routes(buf, A[h], h, H, np.cumsum(orank.quotas3(num16, num8, num4, den, R * R)))
+            log(f"  head {h}: {routes}")
+            assert all(r in (None, ROUTES[kind][0]) for r in routes)
         for a in range(R):
             row = h * R + a
             lists = orank.key_lists_all(want[a])
@@ -83,6 +115,11 @@ def _check(R, scope, kind, budgets, H=2):
 
 
 BUDGETS = (15, 10, 30, 100)
+MIDDLE = [(25, 25, 25, 100), (30, 20, 20, 100), BUDGETS]
+# What the kinds of scores are for, and the budgets it holds for: all but the
+# sampled scores lie above every bracket, or inside the one at the median.
+ROUTES = {"softmax": ("bracket", MIDDLE), "unsampled-high": ("missed", [BUDGETS, (0, 10, 30, 100)]),
+          "unsampled-inside": ("overflow", [(0, 0, 50, 100)])}
 
 
 @pytest.mark.parametrize("scope", ["head", "row"])
@@ -100,6 +137,14 @@ def test_distributions(R, scope, kind):
         pytest.skip("this head is selected without a sample")
     for budgets in (BUDGETS, (0, 10, 30, 100), (0, 0, 50, 100), (1, 998, 0, 1000), (100, 0, 0, 100), (0, 0, 0, 100)):
         _check(R, scope, kind, budgets, H=1)
+
+
+@pytest.mark.parametrize("R", [182, 250, 300, 362])
+@pytest.mark.parametrize("budgets", MIDDLE)
+def test_three_middle_thresholds_of_small_heads(R, budgets):
+    """Three brackets of a sample of 8,192 together hold an eighth of the pairs;
+    the gathered keys have to fit all the same."""
+    _check(R, "head", "softmax", budgets, H=3)
 
 
 @pytest.mark.parametrize("R,scope", [(20, "head"), (200, "head"), (600, "head"), (200, "row")])

@@ -76,11 +76,13 @@ constexpr int kHeadBins = 256, kPicks = kHeadBins + kCuts * kBins;
 static_assert(kPicked + 32 * kCuts <= kHeadBins, "counters fit");
 constexpr int kHeadWords = kCuts * 2048;  // workspace words per head
 static_assert(kPicks + kCuts * kFinal * 2 <= kHeadWords, "bins and picked keys fit");
-// Heads of at least 2^21 scores count and pick their gathered keys with
-// kParts workgroups: one compute unit fetches the ~130,000 keys of R = 1,980 in
-// 20 us a pass (select 44 us; in parts 8 + 9 + 9). At R = 1,260 the two extra
-// launches cost what they save (222 against 218 us for the call, 40 heads).
-constexpr int64_t kPartsKeys = 1 << 21;
+// Heads of at least 13 x 2^17 scores (R = 1,306) count and pick their gathered
+// keys with kParts workgroups: one compute unit fetches the ~130,000 keys of
+// R = 1,980 in 20 us a pass (select 44 us; in parts 8 + 9 + 9). Call without and
+// with parts, two thresholds / three: R = 1,448 x 1 head 71.2 / 83.4 and 63.4 /
+// 66.7 us, 1,350 x 40 268 / 296.5 and 267 / 288; at R = 1,260 x 40 the two extra
+// launches cost what they save (216.5 / 240.7 and 219.9 / 236.0).
+constexpr int64_t kPartsKeys = 13 << 17;
 constexpr int kParts = 8;
 
 // Inclusive key range cut into kBins bins of 2^shift keys.

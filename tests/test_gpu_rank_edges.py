@@ -154,8 +154,9 @@ def test_nan_scores(R, scope):
         _check(R, scope, "nan", budgets, H=1)
 
 
-@pytest.mark.parametrize("R,scope", [(2047, "head"), (2048, "row"), (2049, "row")])
+@pytest.mark.parametrize("R,scope", [(1305, "head"), (1306, "head"), (2047, "head"), (2048, "row"), (2049, "row")])
 def test_longest_rows(R, scope):
-    """The longest head (2^22 pairs less) and row of the register kernels, and
-    the first row that is sorted in LDS."""
+    """The first head whose gathered keys are counted in parts, the longest head
+    (2^22 pairs less) and row of the register kernels, and the first row that is
+    sorted in LDS."""
     _check(R, scope, "softmax", BUDGETS, H=1)

@@ -37,20 +37,35 @@ namespace da2 {
 // Per-channel max|V| of every head. Large heads: a launch clears the entries and
 // prep_vstats takes chunks of tokens with one atomic max per channel (before
 // prep_qk: after it, the pass waits for prep_qk's writes, 26 instead of 16 us on
-// 32,760 tokens x 12 heads, more than the clearing launch costs). Small heads (V
-// of at most kVstatSmall bytes): kVstatParts extra workgroups of the prep_qk
-// launch take a part of the channels each, over all tokens, and store their
-// maxima, which saves both launches (whole layer: 512 tokens x 2 heads 48 -> 42
-// us, 4,255 x 12, d = 64, 105 -> 103; at that size the parts take as long as
-// prep_qk itself), and prep_v derives the head's max|V| from the channels'. Large
-// heads accumulate it with one more atomic.
+// 32,760 tokens x 12 heads, more than the clearing launch costs). Small heads:
+// kVstatParts extra workgroups of the prep_qk launch take a part of the channels
+// each, over all tokens, and store their maxima, which saves both launches (whole
+// layer: 512 tokens x 2 heads 48 -> 42 us, 4,255 x 12, d = 64, 105 -> 103; at
+// that size the parts take as long as prep_qk itself), and prep_v derives the
+// head's max|V| from the channels'. Large heads accumulate it with one more atomic.
 __global__ void zero_vstats_kernel(uint32_t* stats, int d) {
   uint32_t* s = stats + (int64_t)blockIdx.x * (4 + d);
   for (int i = 2 + threadIdx.x; i < 4 + d; i += blockDim.x) s[i] = 0u;
 }
 constexpr int kVstatRows = 1024;  // tokens per workgroup (one atomic max per channel per workgroup)
 constexpr int kVstatParts = 4;
-constexpr int64_t kVstatSmall = 1 << 20;
+// Small: V of one head is at most 1 MiB, which bounds a part's chain of loads,
+// and all heads together are few enough for the parts' access. A part reads
+// D sizeof(T) / 4 bytes of every token row, so 32-byte parts (bf16, d = 64) fetch
+// each 128-byte line four times and 64-byte ones twice. Preparation in launches
+// of its own against parts, us (V bytes x heads):
+//   32 bytes:  256 KiB x 40 23.0, 21.1    256 KiB x 80 32.3, 33.6    512 KiB x 16 20.4, 19.2
+//              512 KiB x 24 24.8, 24.9    1 MiB x 6 20.2, 19.9       1 MiB x 8 20.6, 21.5
+//              1 MiB x 40 51.3, 63.9
+//   64 bytes:  512 KiB x 40 27.6, 25.1    768 KiB x 40 34.4, 33.4    896 KiB x 40 37.8, 38.1
+//              512 KiB x 80 40.9, 41.0    768 KiB x 80 56.0, 59.9    1 MiB x 24 30.1, 28.4
+//   128 bytes: 1 MiB x 40 44.1, 36.8      1 MiB x 80 82.2, 72.0
+template <int D, typename T>
+bool small_heads(int64_t N, int64_t BH) {
+  constexpr int64_t MiB = 1 << 20, part = D * sizeof(T) / kVstatParts;
+  const int64_t v = N * D * (int64_t)sizeof(T), all = v * (BH + 6);
+  return v <= MiB && (part >= 128 || all <= (part >= 64 ? 40 : 12) * MiB);
+}
 
 template <int D, typename T>
 __device__ inline void vstats_part(const PrepArgs& args, int bh, int part) {
@@ -489,7 +504,7 @@ __global__ __launch_bounds__(256) void prep_v_kernel(PrepArgs args) {
 template <int D, typename T>
 void launch_prep_t(const PrepArgs& args, hipStream_t stream) {
   const int BH = args.B * args.H;
-  if ((int64_t)args.N * D * (int64_t)sizeof(T) <= kVstatSmall) {
+  if (small_heads<D, T>(args.N, BH)) {
     hipLaunchKernelGGL((prep_qk_kernel<D, T, true>), dim3(args.R + kVstatParts, BH, 2), dim3(256), 0, stream, args);
     hipLaunchKernelGGL((prep_v_kernel<D, T, true>), dim3(args.R, BH), dim3(256), 0, stream, args);
     return;

@@ -73,6 +73,13 @@ def test_value_statistics_split(dtype, d, n):
                             partition="ragged"))
 
 
+@pytest.mark.parametrize("dtype,n,H", [("bf16", 2048, 42), ("bf16", 2048, 43), ("fp32", 4096, 34), ("fp32", 4096, 35)])
+def test_value_statistics_split_by_heads(dtype, n, H):
+    """The numbers of heads from which narrow rows (d = 64) leave the Q/K launch."""
+    _check_operands(replace(SMALL, name=f"vstats-{dtype}-h{H}", B=1, H=H, d=64, T=1, Hg=1, Wg=n, dtype=dtype,
+                            partition="ragged"))
+
+
 @pytest.mark.parametrize("B,H,T", [(1, 1, 1), (1, 1, 9), (1, 2, 5), (1, 3, 7), (1, 5, 11), (1, 7, 4), (3, 3, 13)])
 def test_rows_dealt_to_xcds(B, H, T):
     """Head counts whose half-heads the eight segments of the work order cut in

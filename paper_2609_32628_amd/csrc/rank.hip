@@ -766,6 +766,19 @@ __global__ __launch_bounds__(1024) void rank_place_kernel(RankArgs args) {
   }
 }
 
+// Work order of row scope, where every row of a group costs the same: head, row
+// parity, row.
+__device__ inline void place_row(const RankArgs& args, int64_t row) {
+  const int R = args.R, a = (int)(row % R);
+  args.order[row - a + (a & 1 ? (R + 1) / 2 : 0) + a / 2] = (int32_t)row;
+}
+
+__device__ inline void write_meta(const RankArgs& args, int64_t row) {
+  if (row != 0) return;
+  args.meta[0] = args.B * args.H * args.R;
+  args.meta[1] = 0;  // error flags of da2_mixed_attn calls on these lists
+}
+
 // ---- classes and lists, one wave per row ------------------------------------------
 // Writes row's classes, ascending lists (4-bit, 8-bit, 16-bit: the phase order
 // of the attention) and counts. xs[st]: the class ranks (0 skip, 1: 4, 2: 8, 3:
@@ -837,17 +850,12 @@ __device__ inline void write_row(const RankArgs& args, int64_t row, const uint32
   }
   if (lane == 0) {
     reinterpret_cast<int4*>(args.counts)[row] = make_int4((int)n4, (int)n8, (int)n16, 0);
-    if (row == 0) {
-      args.meta[0] = args.B * args.H * R;
-      args.meta[1] = 0;  // error flags of da2_mixed_attn calls on these lists
-    }
+    write_meta(args, row);
     if (args.scope == DA2_SCOPE_HEAD) {
       const int32_t cost = row_cost((int)n4, (int)n8, (int)n16);
       args.cost[row] = (int32_t)atomicAdd(args.obins + order_key(args, (uint32_t)row, cost), 1u);
     } else {
-      // every row of a group costs the same: head, row parity, row
-      const int a = (int)(row % R);
-      args.order[row - a + (a & 1 ? (R + 1) / 2 : 0) + a / 2] = (int32_t)row;
+      place_row(args, row);
     }
   }
 }
@@ -1063,9 +1071,7 @@ __global__ __launch_bounds__(256) void rank_row_select_kernel(RankArgs args, int
   }
 }
 
-// Exclusive prefix sum of 64-bit values over an NT-thread block (NT = 64: one
-// wave, no LDS; NT = 256: four waves through LDS).
-template <int NT>
+// Exclusive prefix sum of 64-bit values over a 256-thread block.
 __device__ inline uint64_t block_exscan_u64(uint64_t v, uint64_t* sh, uint64_t* total) {
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   uint64_t x = v;
@@ -1073,53 +1079,44 @@ __device__ inline uint64_t block_exscan_u64(uint64_t v, uint64_t* sh, uint64_t* 
     const uint64_t y = __shfl_up(x, o, 64);
     if (lane >= o) x += y;
   }
-  if constexpr (NT == 64) {
-    *total = __shfl(x, 63, 64);
-    return x - v;
-  } else {
-    if (lane == 63) sh[w] = x;
-    __syncthreads();
-    uint64_t base = 0;
-    for (int q = 0; q < w; ++q) base += sh[q];
-    *total = sh[0] + sh[1] + sh[2] + sh[3];
-    __syncthreads();
-    return base + x - v;
-  }
+  if (lane == 63) sh[w] = x;
+  __syncthreads();
+  uint64_t base = 0;
+  for (int q = 0; q < w; ++q) base += sh[q];
+  *total = sh[0] + sh[1] + sh[2] + sh[3];
+  __syncthreads();
+  return base + x - v;
 }
 
 // Classes, ascending per-row lists (4-bit, then 8-bit, then 16-bit: the phase
-// order of the attention), counts and row cost; one NT-thread workgroup per
-// row (NT = 64 for rows of up to 1024 blocks, 256 beyond). The row's scores are
-// staged in LDS (R floats, dynamic) with coalesced loads; thread i then owns
-// the contiguous run of key blocks [i E, (i + 1) E), E = ceil(R / NT): it
-// classifies its run, a block-wide scan of the packed per-class counts (21
-// bits each) gives every class's write offset, and a second walk over the run
-// writes the lists.
-template <int NT>
-__global__ __launch_bounds__(NT) void rank_classify_kernel(RankArgs args) {
+// order of the attention), counts and work order; one workgroup per row. The
+// row's scores are staged in LDS (R floats, dynamic) with coalesced loads;
+// thread i then owns the contiguous run of key blocks [i E, (i + 1) E),
+// E = ceil(R / 256): it classifies its run, a block-wide scan of the packed
+// per-class counts (21 bits each) gives every class's write offset, and a second
+// walk over the run writes the lists.
+__global__ __launch_bounds__(256) void rank_classify_kernel(RankArgs args) {
   extern __shared__ float srow[];
   __shared__ uint64_t sh[4];
   const int a = blockIdx.x, bh = blockIdx.y, R = args.R, tid = threadIdx.x;
   const int64_t row = (int64_t)bh * R + a;
   const float* A = args.A + row * R;
   // eight loads in flight per thread (indices past the row read its last entry)
-  for (int b0 = tid; b0 < R; b0 += NT * 8) {
+  for (int b0 = tid; b0 < R; b0 += 256 * 8) {
     float v[8];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) v[u] = A[min(b0 + NT * u, R - 1)];
+    for (int u = 0; u < 8; ++u) v[u] = A[min(b0 + 256 * u, R - 1)];
 #pragma unroll
     for (int u = 0; u < 8; ++u)
-      if (b0 + NT * u < R) srow[b0 + NT * u] = v[u];
+      if (b0 + 256 * u < R) srow[b0 + 256 * u] = v[u];
   }
   __syncthreads();
-  const bool head = args.scope == DA2_SCOPE_HEAD;
-  const uint64_t* thr = head ? args.thr + (int64_t)bh * kCuts : args.thr + row * kCuts;
+  const uint64_t* thr = args.thr + row * kCuts;
   const uint64_t t16 = thr[0], t8 = thr[1], t4 = thr[2];
   uint8_t* cls = args.cls + row * R;
   uint16_t* keys = args.keys + row * R;
   auto class_of = [&](int b) -> int {
-    const uint64_t key =
-        head ? rank_key(srow[b], static_cast<uint32_t>(a * R + b)) : rank_key(srow[b], static_cast<uint32_t>(b));
+    const uint64_t key = rank_key(srow[b], static_cast<uint32_t>(b));
     return key >= t16 ? 16 : (key >= t8 ? 8 : (key >= t4 ? 4 : 0));
   };
   constexpr int kF = 21;
@@ -1127,7 +1124,7 @@ __global__ __launch_bounds__(NT) void rank_classify_kernel(RankArgs args) {
   auto field = [](int c) -> uint64_t {
     return c == 4 ? 1ull : (c == 8 ? (1ull << kF) : (c == 16 ? (1ull << (2 * kF)) : 0ull));
   };
-  const int E = (R + NT - 1) / NT;
+  const int E = (R + 255) / 256;
   const int b0 = min(R, tid * E), b1 = min(R, b0 + E);
   uint64_t cnt = 0;
   for (int b = b0; b < b1; ++b) {
@@ -1136,7 +1133,7 @@ __global__ __launch_bounds__(NT) void rank_classify_kernel(RankArgs args) {
     cnt += field(c);
   }
   uint64_t tot;
-  const uint64_t before = block_exscan_u64<NT>(cnt, sh, &tot);
+  const uint64_t before = block_exscan_u64(cnt, sh, &tot);
   const uint32_t n4 = static_cast<uint32_t>(tot & kM), n8 = static_cast<uint32_t>((tot >> kF) & kM),
                  n16 = static_cast<uint32_t>((tot >> (2 * kF)) & kM);
   uint32_t p4 = static_cast<uint32_t>(before & kM);
@@ -1156,63 +1153,8 @@ __global__ __launch_bounds__(NT) void rank_classify_kernel(RankArgs args) {
     args.counts[row * 4 + 1] = n8;
     args.counts[row * 4 + 2] = n16;
     args.counts[row * 4 + 3] = 0;
-    args.cost[row] = row_cost((int)n4, (int)n8, (int)n16);
-  }
-}
-
-__global__ __launch_bounds__(1024) void rank_order_kernel(RankArgs args) {
-  __shared__ uint32_t hist[kOrderBins];
-  __shared__ uint32_t part[1024];
-  constexpr int U = 8;  // row costs in flight per thread
-  const uint32_t n = static_cast<uint32_t>(args.B * args.H) * static_cast<uint32_t>(args.R);
-  for (int i = threadIdx.x; i < kOrderBins; i += 1024) hist[i] = 0u;
-  __syncthreads();
-  for (uint32_t i0 = threadIdx.x; i0 < n; i0 += 1024u * U) {
-    int32_t c[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) c[u] = args.cost[min(i0 + 1024u * u, n - 1u)];
-#pragma unroll
-    for (int u = 0; u < U; ++u)
-      if (i0 + 1024u * u < n) atomicAdd(&hist[order_key(args, i0 + 1024u * u, c[u])], 1u);
-  }
-  __syncthreads();
-  constexpr int per = kOrderBins / 1024;
-  uint32_t s = 0;
-  for (int q = 0; q < per; ++q) s += hist[threadIdx.x * per + q];
-  // exclusive scan of the 1024 per-thread sums: within each wave, then over
-  // the 16 wave totals
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  uint32_t x = s;
-  for (int o = 1; o < 64; o <<= 1) {
-    const uint32_t y = __shfl_up(x, o, 64);
-    if (lane >= o) x += y;
-  }
-  if (lane == 63) part[w] = x;
-  __syncthreads();
-  uint32_t run = x - s;
-  for (int q = 0; q < w; ++q) run += part[q];
-  for (int q = 0; q < per; ++q) {
-    uint32_t v = hist[threadIdx.x * per + q];
-    hist[threadIdx.x * per + q] = run;
-    run += v;
-  }
-  __syncthreads();
-  for (uint32_t i0 = threadIdx.x; i0 < n; i0 += 1024u * U) {
-    int32_t c[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) c[u] = args.cost[min(i0 + 1024u * u, n - 1u)];
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const uint32_t i = i0 + 1024u * u;
-      if (i < n) {
-        const uint32_t pos = atomicAdd(&hist[order_key(args, i, c[u])], 1u);
-        args.order[pos] = static_cast<int32_t>(i);
-      }
-    }
-  }
-  if (threadIdx.x == 0) {
-    args.meta[0] = static_cast<int32_t>(n);
-    args.meta[1] = 0;  // error flags of da2_mixed_attn calls on these lists
+    write_meta(args, row);
+    place_row(args, row);
   }
 }
 
@@ -1283,8 +1225,7 @@ hipError_t launch_rank(const RankArgs& args, hipStream_t stream) {
     int P = 1;
     while (P < R) P <<= 1;
     hipLaunchKernelGGL(rank_row_select_kernel, dim3(R, BH), dim3(256), P * sizeof(uint64_t), stream, args, P);
-    hipLaunchKernelGGL(rank_classify_kernel<256>, dim3(R, BH), dim3(256), R * sizeof(float), stream, args);
-    hipLaunchKernelGGL(rank_order_kernel, dim3(1), dim3(1024), 0, stream, args);
+    hipLaunchKernelGGL(rank_classify_kernel, dim3(R, BH), dim3(256), R * sizeof(float), stream, args);
     return hipGetLastError();
   }
   if (args.scope == DA2_SCOPE_HEAD) {

@@ -215,7 +215,9 @@ int32_t da2_rank_assign_noalloc(const float* A, const da2_problem* p, int32_t nu
  *              by head and by row parity, most expensive first in each group
  *              (cost 3 per 4-bit or 16-bit block and 2 per 8-bit block, the
  *              measured ratio of the attention's per-tile times);
- *              attention workgroup w takes order[(w mod 8)*ceil(n/8) + w div 8]
+ *              the attention splits the order into 8 contiguous segments of
+ *              ceil(n/8) rows, one per XCD; where a segment boundary cuts a
+ *              group in two, the two segments take its rows interleaved
  *              (any permutation of the rows is a valid order)
  *   [3] meta   int32 [8]: [0] = number of rows in order; [1] = error flags
  *              (DA2_ATTN_ERR_*) of da2_mixed_attn calls on these lists,

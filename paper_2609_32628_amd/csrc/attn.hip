@@ -659,9 +659,11 @@ __device__ inline void phase_loop_db(const uint16_t* list, int n, const int32_t*
 // 6 heads 1,971 -> 1,849, 11 heads 3,581 -> 3,457; four and eight heads' segments
 // are whole half-heads. Dealing all entries round-robin balances as well but has
 // every XCD read every head: 3.90 against 3.69 ms at 12 heads. The head of a
-// one-head problem keeps contiguous parts (all its rows run at once), and so do
-// three heads, whose segments each hold parts of two half-heads and no whole one
-// (1,073 us, interleaved 1,121).
+// one-head problem keeps contiguous parts (all its rows run at once). So do three
+// heads, whose segments each hold parts of two half-heads and no whole one:
+// interleaved they are slower than cut by position at R = 588 (1,080 -> 1,125 us)
+// and 1,260 (4,888 -> 5,041; MXFP4 2,638 -> 2,717; d = 64 3,277 -> 3,393), though
+// faster at 196 (225 -> 212), 392 (561 -> 521) and 840 (1,984 -> 1,884).
 __device__ inline int work_entry(int b, int n, int R) {
   const int seg = (n + 7) >> 3, p0 = (b & 7) * seg, pos = p0 + (b >> 3), p1 = min(n, p0 + seg);
   if (pos >= n) return -1;

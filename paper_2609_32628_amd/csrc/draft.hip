@@ -3,7 +3,7 @@
 //   draft_pool     one workgroup per (block, head, Q or K): mean (float64 sum /
 //                  n_a) and channel max over the valid tokens, plus the per-head
 //                  max|Q|, max|K| used by the NVFP4 tensor scales.
-//   draft_logits   128x128 tiles of Qbar Kbar^T / sqrt d or Qmax Kmax^T / sqrt d
+//   draft_logits   128x160 tiles of Qbar Kbar^T / sqrt d or Qmax Kmax^T / sqrt d
 //                  on the float64 matrix cores (16x16x4 MFMA).
 //   draft_rows     short rows: logits and softmaxes of 16 rows in one workgroup.
 //   draft_softmax  one wave per row: the two row softmaxes (max subtracted)

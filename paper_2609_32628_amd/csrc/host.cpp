@@ -99,7 +99,7 @@ void sizes_of(const Dims& d, int32_t scope, int32_t fmt4, int32_t with16, da2_si
   int64_t thr = scope == DA2_SCOPE_ROW ? 8 * da2::kCuts * d.BH * d.R : 8 * da2::kCuts * d.BH;
   s->ws_rank_bytes = align_up(4 * d.BH * da2::kCuts * 2048) + align_up(thr) + align_up(8 * da2::kCuts * d.BH) +
                      align_up(8 * da2::kCuts * d.BH) + align_up(4 * d.BH * d.R) +
-                     align_up(8 * d.BH * da2::kCuts * da2::kRankCand) + align_up(4 * d.BH * da2::kCuts);
+                     align_up(d.BH * da2::kCuts * da2::kRankTailBytes) + align_up(4 * d.BH * da2::kCuts);
   s->ws_prep_bytes = 0;
 }
 
@@ -381,9 +381,9 @@ int32_t rank_launch(const float* A, const Dims& d, int32_t num16, int32_t num8, 
   o += align_up(4 * d.BH * da2::kCuts * 2048);
   a.thr = reinterpret_cast<uint64_t*>(w + o);
   o += align_up(thr);
-  a.prefix = reinterpret_cast<uint64_t*>(w + o);
+  a.bracket_lo = reinterpret_cast<uint64_t*>(w + o);
   o += align_up(8 * da2::kCuts * d.BH);
-  a.kleft = reinterpret_cast<int64_t*>(w + o);
+  a.bracket_hi = reinterpret_cast<uint64_t*>(w + o);
   o += align_up(8 * da2::kCuts * d.BH);
   a.cost = reinterpret_cast<int32_t*>(w + o);
   o += align_up(4 * d.BH * d.R);

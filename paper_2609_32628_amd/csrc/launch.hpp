@@ -29,8 +29,11 @@ struct DraftArgs {
 
 constexpr int kCuts = 3;  // rank cut points: T16, T16+T8, T16+T8+T4
 
-// Sizes the bins of the work order live in (48 KB for one head, 32 KB needed).
-constexpr int kRankCand = 2048;
+// Workspace bytes per (head, cut) behind the rows' places. The bins of the work
+// order (32 KB for all heads) live there; the rest is unused, and the size is
+// kept so that ws_rank_bytes and with it the problems that the scratch-free
+// ranking takes stay what callers know.
+constexpr int64_t kRankTailBytes = 8 * 2048;
 
 struct RankArgs {
   const float* A;
@@ -45,10 +48,10 @@ struct RankArgs {
   // workspace
   uint32_t* hist;          // [BH][kCuts * 2048]: a head's counters
   uint64_t* thr;           // head: [BH][kCuts]; row: [BH*R][kCuts]
-  uint64_t* prefix;        // [BH][kCuts]: lower ends of the threshold brackets
-  int64_t* kleft;          // [BH][kCuts]: upper ends
+  uint64_t* bracket_lo;    // [BH][kCuts]: ends of the threshold brackets (keys inside)
+  uint64_t* bracket_hi;    // [BH][kCuts]
   uint32_t* obins;         // rows per bin of the work order
-  int32_t* cost;           // [BH*R]: row's place inside its bin (long rows: its cost)
+  int32_t* cost;           // [BH*R]: a row's place inside its bin (head scope)
 };
 
 struct PrepArgs {

@@ -9,7 +9,8 @@
 // with key >= key of rank cut2 (1-based ranks; an empty cut matches nothing).
 //
 // Head scope reads the R^2 scores of a head twice:
-//   sample    all workgroups: 32,768 scores of every head;
+//   sample    all workgroups: 32,768 scores of every head (8,192 of heads of up
+//             to 362 blocks);
 //   bracket   one workgroup per cut: order statistics of the sample bracket
 //             every threshold key;
 //   collect   all workgroups: counts the keys above each bracket and gathers
@@ -17,15 +18,16 @@
 //   select    one workgroup per cut: the threshold key, exactly, from the
 //             gathered keys (from the scores themselves when the bracket missed
 //             or the keys did not fit);
-//   classify  classes, lists, counts, and the histogram of the row costs;
-//   order     the attention work order from that histogram.
-// At R = 1,980 x 24 heads the call takes 290 us (620 with three histogram
-// passes over all scores): sample 20, bracket 15, collect 100, count and pick
-// 17, select 9, classify 121, order 5; the map's two reads and the results are
-// 940 MB. At R = 588 x 12 heads 54 us (75).
+//   rows      classes, lists, counts, and the histogram of the row costs;
+//   place     the attention work order from that histogram.
+// Long heads count and pick the gathered keys with several workgroups per head
+// before select. At R = 1,980 x 24 heads the call takes 286 us (620 with three
+// histogram passes over all scores): sample 20, bracket 15, collect 100, count
+// and pick 17, select 9, rows 121, place 5; the map's two reads and the results
+// are 940 MB. At R = 588 x 12 heads 54 us (77).
 // Heads of up to kDirectKeys scores go straight to select. Row scope is one
 // launch: a wave per row selects, classifies and writes the lists (R <= 2048;
-// longer rows sort their keys in LDS).
+// longer rows sort their keys in LDS and are classified by a workgroup each).
 #include <algorithm>
 #include <cmath>
 #include <mutex>
@@ -67,6 +69,7 @@ constexpr int kMaxPerThread = 32;  // of the bracket's 1024 threads
 // with a sample.
 constexpr int64_t kDirectKeys = 4 * 8192 + 64;
 constexpr int kOrderBins = 8192;       // bins of the work order
+static_assert(4 * kOrderBins <= kCuts * kRankTailBytes, "the bins fit one head's part of the workspace");
 constexpr int kFinal = 448;             // keys select ranks by counting
 // A head's words in the workspace: counters 128 bytes apart (keys above each
 // bracket, keys gathered, keys picked), then the bins and the picked keys of
@@ -310,8 +313,8 @@ __global__ __launch_bounds__(1024) void rank_bracket_kernel(RankArgs args, doubl
     __syncthreads();
   }
   if (tid == 0) {
-    args.prefix[bh * kCuts + t] = s_lo[1];
-    args.kleft[bh * kCuts + t] = (int64_t)s_hi[0];
+    args.bracket_lo[bh * kCuts + t] = s_lo[1];
+    args.bracket_hi[bh * kCuts + t] = s_hi[0];
   }
 }
 
@@ -340,8 +343,8 @@ __global__ __launch_bounds__(256) void rank_collect_kernel(RankArgs args, int ch
 #pragma unroll
   for (int t = 0; t < kCuts; ++t) {
     active[t] = args.cut[t] > 0 && args.cut[t] < M;
-    lo[t] = args.prefix[bh * kCuts + t];
-    hi[t] = (uint64_t)args.kleft[bh * kCuts + t];
+    lo[t] = args.bracket_lo[bh * kCuts + t];
+    hi[t] = args.bracket_hi[bh * kCuts + t];
     if (!active[t]) lo[t] = hi[t] = kNone;  // no key is inside or above
   }
   __syncthreads();
@@ -483,8 +486,8 @@ __global__ __launch_bounds__(1024) void rank_count_kernel(RankArgs args) {
 #pragma unroll
   for (int t = 0; t < kCuts; ++t) {
     active[t] = args.cut[t] > 0 && args.cut[t] < M;
-    lo[t] = args.prefix[bh * kCuts + t];
-    span[t] = (uint64_t)args.kleft[bh * kCuts + t] - lo[t];
+    lo[t] = args.bracket_lo[bh * kCuts + t];
+    span[t] = args.bracket_hi[bh * kCuts + t] - lo[t];
     sh[t] = range_shift(lo[t], lo[t] + span[t]);
     bins[t][tid] = 0u;
   }
@@ -514,7 +517,7 @@ __global__ __launch_bounds__(1024) void rank_pick_kernel(RankArgs args) {
   if (n > cap) return;
   part_share(n, &i0, &i1);
   if (w < kCuts) {
-    uint64_t l = args.prefix[bh * kCuts + w], h = (uint64_t)args.kleft[bh * kCuts + w];
+    uint64_t l = args.bracket_lo[bh * kCuts + w], h = args.bracket_hi[bh * kCuts + w];
     int64_t k = args.cut[w] - (int64_t)hw[kAbove + 32 * w];
     uint32_t cnt = 0;
     const bool ok = args.cut[w] > 0 && args.cut[w] < M && narrow(hw + kHeadBins + w * kBins, l, h, k, cnt);
@@ -638,8 +641,8 @@ __global__ __launch_bounds__(1024) void rank_select_kernel(RankArgs args, int sa
   if (tid == 0) s_n = 0u;
   if (from_list) {
     if (tid == 0) {
-      s_lo = args.prefix[bh * kCuts + t];
-      s_hi = (uint64_t)args.kleft[bh * kCuts + t];
+      s_lo = args.bracket_lo[bh * kCuts + t];
+      s_hi = args.bracket_hi[bh * kCuts + t];
       s_k = cut - (int64_t)hw[kAbove + 32 * t];
       s_open = 1;
       s_fail = 0;
@@ -704,11 +707,11 @@ __global__ __launch_bounds__(1024) void rank_select_kernel(RankArgs args, int sa
 
 // ---- work order ------------------------------------------------------------------
 // Rows are grouped by head and, inside a head, by row parity (two half-heads
-// with near-equal cost); each group is sorted most expensive first. The
-// attention launch hands workgroup b the entry (b mod 8) * ceil(n/8) + b div 8,
-// and workgroups are dispatched round-robin over the 8 XCDs, so each XCD walks
-// one contiguous segment (about n/8 rows of one or two heads, whose K/V then
-// share that XCD's L2) longest-first.
+// with near-equal cost); each group is sorted most expensive first. Workgroups
+// are dispatched round-robin over the 8 XCDs, and the attention launch gives each
+// XCD one contiguous segment of the order (about n/8 rows of one or two heads,
+// whose K/V then share that XCD's L2), which it walks longest-first; a half-head
+// that two segments share is dealt to both by cost (work_entry in attn.hip).
 // Bin of row i (cost c) in the work order. 32-bit arithmetic: rows number
 // fewer than 2^31 and R <= 65535 (both checked on the host), so c (n4 + n8 +
 // n16 <= R blocks at most 3 each) times the bins per group (<= 4096) and the
@@ -1162,7 +1165,7 @@ __global__ __launch_bounds__(256) void rank_classify_kernel(RankArgs args) {
 // every workspace array of the ranking lives here instead of in a caller
 // buffer. Each device holds its own copy for the life of the process; calls
 // on one device share it, so such calls must not overlap on that device. The
-// kernels clear what must start at zero (rank_init_kernel), so no state from
+// kernels clear what must start at zero (the first launch of head scope), so no state from
 // an earlier call is read.
 static __device__ __align__(256) uint8_t scratch[kRankScratchBytes];
 
@@ -1247,6 +1250,10 @@ hipError_t launch_rank(const RankArgs& args, hipStream_t stream) {
     }
     hipLaunchKernelGGL(rank_select_kernel, dim3(kCuts, BH), dim3(1024), 0, stream, args, (int)sampled, (int)parted);
   }
+  // steps of 256 pairs a wave holds; a row with 4, 6 or 7 steps takes the next
+  // larger form (forms of their own, 12 heads: R = 1,024 head scope 97.3 -> 95.8,
+  // row scope 62.5 -> 53.3 us; 1,536 133.7 -> 129.2, 144.9 -> 110.3; each adds
+  // 48 KB of code)
   const int st = (R + 255) / 256;
   if (st <= 1)
     launch_rows<1>(args, stream);

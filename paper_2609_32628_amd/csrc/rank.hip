@@ -57,6 +57,8 @@ typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
 typedef uint32_t u32u1 __attribute__((aligned(1), may_alias));
 typedef uint32_t u32u2 __attribute__((aligned(2), may_alias));
 typedef uint32_t u32a __attribute__((may_alias));
+// Counts of a row; the lists' base is aligned to 4 bytes only.
+typedef int32_t i32x4u __attribute__((ext_vector_type(4), aligned(4), may_alias));
 
 // ---- head scope: threshold keys ------------------------------------------------
 constexpr int kBins = 1024;            // bins of a key range
@@ -764,7 +766,7 @@ __global__ __launch_bounds__(1024) void rank_place_kernel(RankArgs args) {
   __syncthreads();
   const uint32_t i = blockIdx.x * 1024u + tid;
   if (i < n) {
-    const int4 k = reinterpret_cast<const int4*>(args.counts)[i];
+    const i32x4u k = reinterpret_cast<const i32x4u*>(args.counts)[i];
     args.order[first[order_key(args, i, row_cost(k.x, k.y, k.z))] + (uint32_t)args.cost[i]] = (int32_t)i;
   }
 }
@@ -852,7 +854,7 @@ __device__ inline void write_row(const RankArgs& args, int64_t row, const uint32
       keys[i] = keys_l[i];
   }
   if (lane == 0) {
-    reinterpret_cast<int4*>(args.counts)[row] = make_int4((int)n4, (int)n8, (int)n16, 0);
+    reinterpret_cast<i32x4u*>(args.counts)[row] = i32x4u{(int)n4, (int)n8, (int)n16, 0};
     write_meta(args, row);
     if (args.scope == DA2_SCOPE_HEAD) {
       const int32_t cost = row_cost((int)n4, (int)n8, (int)n16);

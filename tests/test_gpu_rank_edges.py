@@ -147,6 +147,26 @@ def test_three_middle_thresholds_of_small_heads(R, budgets):
     _check(R, "head", "softmax", budgets, H=3)
 
 
+@pytest.mark.parametrize("scope", ["head", "row"])
+def test_lists_aligned_to_four_bytes(scope):
+    """The lists' entries are 32 bits at most: a base between 16-byte marks."""
+    R, H = 75, 2
+    p = api.problem(1, H, 64, R, 7, 8)
+    buf = api.alloc(p, scope)
+    buf.A.copy_(torch.from_numpy(np.stack([_scores("softmax", R, h) for h in range(H)])[None]))
+    raw = torch.full((buf.lists.numel() + 16,), 0xA5, dtype=torch.uint8, device="cuda")
+    at = raw[4:4 + buf.lists.numel()]
+    for lists in (buf.lists, at):
+        lists.fill_(0xA5)
+        api.da2_rank_assign(buf.A, p, *BUDGETS, scope, buf.cls, lists, buf.ws_rank)
+    torch.cuda.synchronize()
+    (keys, counts, order), buf.lists = lists_of(buf, p), at
+    keys4, counts4, order4 = lists_of(buf, p)
+    assert np.array_equal(counts, counts4) and np.array_equal(keys, keys4)
+    assert np.array_equal(np.sort(order4), np.arange(H * R))
+    assert (raw[:4] == 0xA5).all() and (raw[4 + buf.lists.numel():] == 0xA5).all()
+
+
 @pytest.mark.parametrize("R,scope", [(20, "head"), (200, "head"), (600, "head"), (200, "row")])
 def test_nan_scores(R, scope):
     """Every threshold among equal scores of the largest image, and one below."""

@@ -74,6 +74,15 @@ def test_hardware_fp8_conversion_is_rne_in_range(probe):
     assert bad.size == 0, [(x[inr][i], got[i], want[i]) for i in bad[:10]]
 
 
+def test_hardware_fp8_conversion_up_to_464(probe):
+    """... and between 448 and the midpoint to the next binade's 480, which 8-bit
+    weights reach by the rounding of their exponent: 448."""
+    x, o = probe
+    inr = (np.abs(x) > 448.0) & (np.abs(x) < 464.0)
+    assert inr.sum() > 100 and np.abs(x[inr]).max() == np.nextafter(np.float32(464), np.float32(0))
+    assert np.array_equal(o["e4m3_hw"][inr].astype(np.uint8), F.e4m3_code(np.copysign(448.0, x[inr])))
+
+
 def test_int8_code(probe):
     """The INT8 encoder's rounding (operand preparation): round half away from
     zero, clamped to [-127, 127], on every integer +- 0.5 tie up to 130, their

@@ -497,12 +497,13 @@ __device__ inline void nv_phase_loop(const uint16_t* list, int n, const int32_t*
 // 3.83 ms at d = 128 and 2.28 -> 2.13 at d = 64; all pairs 9.33 -> 8.78. Bit-
 // identical outputs.
 // Frag: fragment type; NFK: fragments per K (and V) tile; SA: logit tile type.
-// first(S): logits of the first block. region1<MASK>(S, S', nb) (MASK: block i
-// is partial); pv(S): the value product of block i.
+// first(S): logits of the first block. region1<MASK>(S, S', nb) (MASK: 0 if block
+// i is full, else 1, or 2 with select: a branch inside a region would split its
+// schedule); pv(S): the value product of block i.
 template <int NFK, typename Frag, typename SA, typename FIRST, typename STEP1, typename PV>
 __device__ inline void phase_loop(const uint16_t* list, int n, const int32_t* n_a, const float* dKh,
                                   const Frag* Kh, const Frag* Vh, Frag* sK, Frag* sV, int wave, int lane,
-                                  FIRST first_qk, STEP1 region1, PV pv) {
+                                  bool select, FIRST first_qk, STEP1 region1, PV pv) {
   constexpr int TILE = NFK * 64;       // fragments per tile
   constexpr int W0 = (NFK + 1) / 2;    // fragments wave 0 copies; wave 1 copies the rest
   // Wave 0 copies fragments [0, W0) of a tile, wave 1 the rest; fragment i of
@@ -546,10 +547,12 @@ __device__ inline void phase_loop(const uint16_t* list, int n, const int32_t* n_
     dma_tile(Vh + (int64_t)kb0 * TILE, sV);
     // On the last block the logits of the region are computed from the
     // unchanged tile and not used.
-    if (nb < kCap)
-      region1.template operator()<true>(Sc, Sn, nb);
+    if (nb == kCap)
+      region1.template operator()<0>(Sc, Sn, nb);
+    else if (!select)
+      region1.template operator()<1>(Sc, Sn, nb);
     else
-      region1.template operator()<false>(Sc, Sn, nb);
+      region1.template operator()<2>(Sc, Sn, nb);
     wait_vmem();
     wait_lds();
     wg_barrier();  // V(i) copied; both waves are done with sK
@@ -1129,13 +1132,9 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(2))) void m
     float gm0 = 0.0f, gm1 = 0.0f, mn = 0.0f, sum0 = 0.0f, sum1 = 0.0f;
     // Region 1: logits of the next block with the maxima and the first
     // group's weights of the current block (four pieces over the stages).
-    auto region1 = [&]<bool MASK>(SA& Sc, SA& Sn, int nb) {
-      if constexpr (MASK) {
-        if (__builtin_expect(unbounded, 0))
-          mask_tail_select(Sc, nb, g);
-        else
-          mask_tail(Sc, nb, row_slot(r), row_slot(r) + 32, lane);
-      }
+    auto region1 = [&]<int MASK>(SA& Sc, SA& Sn, int nb) {
+      if constexpr (MASK == 1) mask_tail(Sc, nb, row_slot(r), row_slot(r) + 32, lane);
+      if constexpr (MASK == 2) mask_tail_select(Sc, nb, g);
       f16x8 k0 = sK[lane], k1 = sK[NS16 * 64 + lane];
       constexpr int NP = 4;
       sum0 = 0.0f;
@@ -1203,7 +1202,7 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(2))) void m
     phase_loop<2 * NS16, f16x8, SA>(keys + n4 + n8, n16, L.n_a, dKh,
                                     reinterpret_cast<const f16x8*>(args.K16) + blk0 * (kCap * D / 8),
                                     reinterpret_cast<const f16x8*>(args.V16) + blk0 * (kCap * D / 8), sK, sV, wave,
-                                    lane, qk, region1, pv);
+                                    lane, unbounded, qk, region1, pv);
   }
 
   // ------------------------- normalize and scatter -------------------------

@@ -24,8 +24,10 @@ FLAGS = [
 ]
 
 
-# The attention and draft kernels never produce NaN (finite operands, -inf only
-# for masked logits and padding), so max/min need no NaN canonicalization there.
+# No maximum or minimum of the attention and draft kernels sees a NaN: operands
+# are finite and -inf marks masked logits and padding (16-bit padding logits of
+# an infinite query, which are NaN, are replaced on their bits before the first
+# maximum), so none needs NaN canonicalization.
 EXTRA = {"attn.hip": ["-fno-honor-nans"], "draft.hip": ["-fno-honor-nans"]}
 
 

@@ -130,11 +130,12 @@ __device__ inline float e4m3_round_hw(float a) {
   return __builtin_amdgcn_cvt_f32_fp8(__builtin_amdgcn_cvt_pk_fp8_f32(a, 0.0f, __float_as_int(a), false), 0);
 }
 __device__ inline void fp4_setup(Fp4Group& G, float gmax, float c, float mn) {
-  // mn is a rounded product and the fused one is not, so pmax exceeds 1 by up to
+  // mn is a rounded product and the fused one is not, so max Pt exceeds 1 by up to
   // half an ulp of mn in the exponent: without the clamp 448 pmax passes 464 from
-  // |mn| = 2^20 on (constant Q = K = 344), where the conversion returns NaN
-  const float pmax = exp2_fast(__builtin_fmaf(gmax, c, -mn));
-  const float sigma = e4m3_round_hw(fminf(448.0f * pmax, 448.0f));
+  // |mn| = 2^20 on (constant Q = K = 344), where the conversion returns NaN. The
+  // clamp is the exponential's output modifier and takes no instruction.
+  const float pmax = __builtin_amdgcn_fmed3f(exp2_fast(__builtin_fmaf(gmax, c, -mn)), 0.0f, 1.0f);
+  const float sigma = e4m3_round_hw(448.0f * pmax);
   const float sg = fmaxf(sigma, kE4m3Min);
   G.off = (kLog2_2688 - __builtin_amdgcn_logf(sg)) - mn;
   G.scale = sg * (1.0f / 2688.0f);

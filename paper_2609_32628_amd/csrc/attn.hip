@@ -488,19 +488,33 @@ __device__ inline void nv_phase_loop(const uint16_t* list, int n, const int32_t*
 // tiles of each key block are copied into LDS once (each wave issues half of
 // the fragments) and read by both waves. One K and one V tile fit (16 KB each
 // at d = 128). Iteration i:
-//   wait K(i+1) -> barrier -> copy V(i) -> region 1: S' = K(i+1) Q^T beside the
-//   first half of the softmax of S
-//   -> wait V(i) -> barrier -> copy K(i+2) -> U += V(i)^T P^T beside the second
-//   half
-// Two barriers per block, and each copy has one region to arrive. With the
+//   wait K(i+1) -> barrier -> region 1: S' = K(i+1) Q^T beside the first half of
+//   the softmax of S, and the copy of V(i)
+//   -> wait V(i) -> barrier -> U += V(i)^T P^T beside the second half, and the
+//   copy of K(i+2)
+// Two barriers per block, and each copy has the rest of its region to arrive. With the
 // second half of the softmax in a stage of its own and four barriers, no matrix
 // work ran beside it: 588 blocks x 12 heads, 40% of the pairs 16-bit, 4.07 ->
 // 3.83 ms at d = 128 and 2.28 -> 2.13 at d = 64; all pairs 9.33 -> 8.78. Bit-
 // identical outputs.
+// Where in its region a copy is issued (the callers' kCopyAt) decides whether the
+// workgroups of an XCD stay together. They walk the same or similar lists, and one
+// that is ahead fetches each block from beyond L2. If the region still covers that
+// latency, nothing slows it down, the workgroups drift apart until their spread
+// exceeds the L2 (128 blocks of K and V), and every one of them waits for the memory
+// beyond it. A quarter into the region (d = 128) the leader waits and the others,
+// who hit, do not. Attention call with 50 / 70 / 100% of the pairs 16-bit, ms, copies
+// before the region, at its start, a quarter and half into it:
+//   R = 1,736 ragged, 16 heads  55 / 107 / 152   55 / 78 / 107   55 / 76 / 105   67 / 91 / 105
+//   R = 1,860, 24 heads         97 / 155 / 230   98 / 150 / 195  99 / 150 / 180  123 / 170 / 184
+//   R = 588, 12 heads           4.6 / 6.1 / 9.0  4.5 / 6.1 / 8.7 4.4 / 6.0 / 8.6 4.5 / 6.1 / 8.6
+// d = 64, where a region is half as long, before, at the start and a quarter into it:
+//   R = 1,860, 16 heads         37 / 51 / 74     36 / 50 / 74    37 / 53 / 71
+//   R = 588, 12 heads           2.90 / 3.91 / 5.41  2.89 / 3.86 / 5.40  2.92 / 3.97 / 5.46
 // Frag: fragment type; NFK: fragments per K (and V) tile; SA: logit tile type.
-// first(S): logits of the first block. region1<MASK>(S, S', nb) (MASK: 0 if block
-// i is full, else 1, or 2 with select: a branch inside a region would split its
-// schedule); pv(S): the value product of block i.
+// first(S): logits of the first block. region1<MASK>(S, S', nb, copy) (MASK: 0 if
+// block i is full, else 1, or 2 with select: a branch inside a region would split
+// its schedule); pv(S, copy): the value product of block i. Both call copy() once.
 template <int NFK, typename Frag, typename SA, typename FIRST, typename STEP1, typename PV>
 __device__ inline void phase_loop(const uint16_t* list, int n, const int32_t* n_a, const float* dKh,
                                   const Frag* Kh, const Frag* Vh, Frag* sK, Frag* sV, int wave, int lane,
@@ -545,20 +559,22 @@ __device__ inline void phase_loop(const uint16_t* list, int n, const int32_t* n_
     wait_vmem();
     wait_lds();
     wg_barrier();  // K(i+1) copied; both waves are done with sV
-    dma_tile(Vh + (int64_t)kb0 * TILE, sV);
+    auto copy_v = [&]() { dma_tile(Vh + (int64_t)kb0 * TILE, sV); };
+    auto copy_k = [&]() {
+      if (more2) dma_tile(Kh + (int64_t)kb2 * TILE, sK);
+    };
     // On the last block the logits of the region are computed from the
     // unchanged tile and not used.
     if (nb == kCap)
-      region1.template operator()<0>(Sc, Sn, nb);
+      region1.template operator()<0>(Sc, Sn, nb, copy_v);
     else if (!select)
-      region1.template operator()<1>(Sc, Sn, nb);
+      region1.template operator()<1>(Sc, Sn, nb, copy_v);
     else
-      region1.template operator()<2>(Sc, Sn, nb);
+      region1.template operator()<2>(Sc, Sn, nb, copy_v);
     wait_vmem();
     wait_lds();
     wg_barrier();  // V(i) copied; both waves are done with sK
-    if (more2) dma_tile(Kh + (int64_t)kb2 * TILE, sK);
-    pv(Sc);
+    pv(Sc, copy_k);
   };
   for (int it = 0; it < n; it += 2) {
     step(it, Sa, Sb);
@@ -1119,6 +1135,7 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(2))) void m
       for (int e = 0; e < 4; ++e) top |= (static_cast<uint32_t>(x[e]) & 0x7C007C00u) + 0x04000400u;
     }
     const bool unbounded = __ballot((top & 0x80008000u) != 0) != 0;
+    constexpr int kCopyAt = D == 128 ? 1 : 0;  // quarter of a region at which it issues its copy
     f16x8 P[4];
     float alpha = 1.0f;
     typedef f32x16 SA[2];
@@ -1133,7 +1150,7 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(2))) void m
     float gm0 = 0.0f, gm1 = 0.0f, mn = 0.0f, sum0 = 0.0f, sum1 = 0.0f;
     // Region 1: logits of the next block with the maxima and the first
     // group's weights of the current block (four pieces over the stages).
-    auto region1 = [&]<int MASK>(SA& Sc, SA& Sn, int nb) {
+    auto region1 = [&]<int MASK>(SA& Sc, SA& Sn, int nb, auto copy) {
       if constexpr (MASK == 1) mask_tail(Sc, nb, row_slot(r), row_slot(r) + 32, lane);
       if constexpr (MASK == 2) mask_tail_select(Sc, nb, g);
       f16x8 k0 = sK[lane], k1 = sK[NS16 * 64 + lane];
@@ -1141,6 +1158,7 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(2))) void m
       sum0 = 0.0f;
 #pragma unroll
       for (int s = 0; s < NS16; ++s) {
+        if (s == NS16 * kCopyAt / 4) copy();
         f16x8 n0 = k0, n1 = k1;
         if (s + 1 < NS16) {
           n0 = sK[(s + 1) * 64 + lane];
@@ -1169,7 +1187,7 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(2))) void m
     };
     // U += V^T P^T; value fragments are read two MFMAs ahead. The MFMAs of the
     // first group (k < 2 NT) carry the second group's weights.
-    auto pv = [&](SA& Sc) {
+    auto pv = [&](SA& Sc, auto copy) {
       if (__ballot(alpha != 1.0f)) rescale<NT>(U, alpha);
       constexpr int NM = 4 * NT;
       auto vfrag = [&](int k) { return sV[((k % NT) * 4 + k / NT) * 64 + lane]; };
@@ -1177,6 +1195,7 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(2))) void m
       sum1 = 0.0f;
 #pragma unroll
       for (int k = 0; k < NM; ++k) {
+        if (k == NM * kCopyAt / 4) copy();
         const f16x8 cur = (k & 1) ? v1 : v0;
         if (k + 2 < NM) {
           if (k & 1)
